@@ -33,6 +33,10 @@
 // and sets the range's counters up for the next call.  Its first workgroup
 // publishes the call's status word and advances the epoch.
 //
+// The SGD update from one payload needs neither grouping nor ranges: its
+// indices are distinct, so every pair updates its own coordinate in one
+// launch (apply_direct_kernel).
+//
 // Counters carry a tag of the call's epoch, so that a counter left by an
 // earlier call (or any other content) reads as zero and no clearing pass is
 // needed; once a call has completed, every counter holds the next epoch's
@@ -92,6 +96,10 @@ constexpr uint64_t kFlagsTagIndex = ~uint64_t(0) - 1;
 //                  clean, written by the first launch for the later ones;
 //   flags          added to by the first launch;
 //   status         written by the range launch.
+// The single-launch update (apply_direct_kernel) has words of its own, tagged
+// with its own epoch, so that it leaves the counters' epoch alone; its last
+// workgroup writes status.
+constexpr int kDirectTickets = 16;
 struct ApplyCtl {
     unsigned long long epoch;  // epoch of the next call (40 bits)
     unsigned long long flags;  // status bits noted during a call, tagged with its epoch
@@ -100,7 +108,10 @@ struct ApplyCtl {
     uint32_t status;           // status bits of the last completed call
     uint32_t run_clean;        // 1 when this call's counters started clean
     unsigned long long run_epoch;   // epoch of the call in progress
-    uint32_t pad[54];
+    unsigned long long direct_epoch, direct_flags, direct_clean;
+    // finished workgroups b = i mod kDirectTickets in word i; finished words last
+    unsigned long long direct_ticket[kDirectTickets + 1];
+    uint32_t pad[14];
 };
 static_assert(sizeof(ApplyCtl) == 256, "control block is 256 bytes");
 
@@ -158,16 +169,19 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v) {
 }
 
 // Adds `len` to a tagged counter word: a word with another tag counts as
-// zero.  Returns the count before the addition.
+// zero.  Returns the count before the addition.  Only the adds of one call
+// follow a word's first one with the call's tag, so those are plain atomic
+// adds: a compare-and-swap loop for every add cost a first call on a new
+// workspace a retry per contender (1024 workgroups taking tickets: 442 us a
+// step of 1.1e8 elements, 321 so).
 __device__ __forceinline__ uint64_t tagged_add(unsigned long long *w, uint64_t tag, uint64_t len) {
     unsigned long long cur = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    for (;;) {
-        const uint64_t base = (cur >> kEpochShift) == tag ? (cur & kCountBits) : 0;
-        const unsigned long long want = (tag << kEpochShift) | ((base + len) & kCountBits);
-        const unsigned long long got = atomicCAS(w, cur, want);
-        if (got == cur) return base;
+    while ((cur >> kEpochShift) != tag) {
+        const unsigned long long got = atomicCAS(w, cur, (unsigned long long)(tag << kEpochShift) | len);
+        if (got == cur) return 0;
         cur = got;
     }
+    return len != 0 ? atomicAdd(w, (unsigned long long)len) & kCountBits : cur & kCountBits;
 }
 
 // Adds `len` to counter e of the call of `epoch` and returns the count
@@ -637,6 +651,100 @@ __global__ __launch_bounds__(kBlock) void apply_range_kernel(RangeArgs a) {
     }
 }
 
+// SGD update from one payload: x[i] -= 0 + v for every pair (the sum of one
+// value started at +0, as the range launch forms it), kPairsPerThread pairs a
+// thread in flight.  Bound by the scattered lines of x, one read and one
+// write each.  Against the place and range launches: 1.5e6 pairs over 1.5e9
+// coordinates 526 -> 92 us, 1.1e6 over 1.1e8 133 -> 58, 25,557 over 25.6e6
+// 14.6 -> 5.9, 50 over 5,000 6.0 -> 2.2 (the range launch visits every range
+// of d, here only the payload is read).
+// The last workgroup to finish publishes the status word.  One word of
+// tickets would serialise the grid's atomics at 13 ns each, so they go to
+// kDirectTickets words first and the last of each takes one of the final word.
+__device__ __forceinline__ uint64_t direct_tag(uint64_t epoch, int i) {
+    return counter_tag(epoch, ~uint64_t(0) - 16 - uint64_t(i));
+}
+
+__global__ __launch_bounds__(kBlock) void apply_direct_kernel(const int32_t *__restrict__ idx,
+                                                              const float *__restrict__ val,
+                                                              const uint32_t *__restrict__ count,
+                                                              int64_t cap, int64_t d,
+                                                              float *__restrict__ x,
+                                                              ApplyCtl *__restrict__ ctl) {
+    __shared__ uint32_t s_flags;
+    const int64_t have = count != nullptr ? int64_t(*count) : cap;
+    const uint64_t epoch = ctl->direct_epoch & kEpochMask;
+    const bool clean = ctl->direct_clean == clean_key(epoch, kDirectTickets + 1);
+    const int64_t c = have < cap ? have : cap;
+    // one pair a thread while the grid covers them so, else kPairsPerThread;
+    // workgroups without pairs leave at once (the first stays)
+    const bool few = c <= int64_t(gridDim.x) * kBlock;
+    const int64_t batch = few ? kBlock : kPairBatch;
+    const int64_t need = (c + batch - 1) / batch;
+    const uint32_t G = uint32_t(need < 1 ? 1 : need < gridDim.x ? need : gridDim.x);
+    if (blockIdx.x >= G) return;
+    if (threadIdx.x == 0) s_flags = have > cap ? kSparseTruncated : 0u;
+    __syncthreads();
+    bool bad = false;
+    for (int64_t base = int64_t(blockIdx.x) * batch; base < c; base += int64_t(G) * batch) {
+        int32_t i[kPairsPerThread];
+        float v[kPairsPerThread], xv[kPairsPerThread];
+#pragma unroll
+        for (int q = 0; q < kPairsPerThread; ++q) {
+            const int64_t j = base + q * kBlock + threadIdx.x;
+            i[q] = -1;
+            v[q] = 0.0f;
+            if (j < c && (q == 0 || !few)) {
+                i[q] = idx[j];
+                v[q] = val[j];
+                if (i[q] < 0 || int64_t(i[q]) >= d) {
+                    bad = true;
+                    i[q] = -1;
+                }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < kPairsPerThread; ++q) xv[q] = i[q] >= 0 ? x[i[q]] : 0.0f;
+#pragma unroll
+        for (int q = 0; q < kPairsPerThread; ++q)
+            if (i[q] >= 0) x[i[q]] = __fsub_rn(xv[q], __fadd_rn(0.0f, v[q]));
+    }
+    if (bad) atomicOr(&s_flags, kSparseBadIndex);
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    const uint64_t flags_tag = direct_tag(epoch, kDirectTickets + 1);
+    if (G > 1) {
+        auto ticket = [&](int i) -> uint64_t {
+            unsigned long long *w = &ctl->direct_ticket[i];
+            if (clean) return atomicAdd(w, 1ull) & kCountBits;
+            return tagged_add(w, direct_tag(epoch, i), 1);
+        };
+        if (s_flags) {
+            tagged_add(&ctl->direct_flags, flags_tag, 0);
+            atomicOr(&ctl->direct_flags, (unsigned long long)s_flags);
+            __threadfence();   // noted before the ticket that the last workgroup sees
+        }
+        if (G > uint32_t(kDirectTickets)) {
+            const uint32_t word = blockIdx.x % kDirectTickets;
+            const uint32_t members = (G - word + kDirectTickets - 1) / kDirectTickets;
+            if (ticket(int(word)) != members - 1) return;
+            __threadfence();
+        }
+        if (ticket(kDirectTickets) != min(G, uint32_t(kDirectTickets)) - 1) return;
+        __threadfence();
+        const unsigned long long f =
+            __hip_atomic_load(&ctl->direct_flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        ctl->status = (f >> kEpochShift) == flags_tag ? uint32_t(f & 0xffu) : 0u;
+        const uint64_t next = (epoch + 1) & kEpochMask;
+        for (int i = 0; i <= kDirectTickets; ++i)
+            ctl->direct_ticket[i] = direct_tag(next, i) << kEpochShift;
+        ctl->direct_clean = clean_key(next, kDirectTickets + 1);
+        ctl->direct_epoch = next;
+    } else {
+        ctl->status = s_flags;   // this workgroup saw every pair
+    }
+}
+
 template <int kMode>
 void launch_range(bool bucketed, uint32_t grid, const RangeArgs &a, hipStream_t stream) {
     if (bucketed)
@@ -680,6 +788,16 @@ hipError_t launch_apply(const int32_t *const *idx, const float *const *val,
     uint2 *pairs = reinterpret_cast<uint2 *>(ws + L.pair_off);
 
     const int cus = device_cu_count();
+    if (n == 1 && mode == 1) {
+        // a payload of its whole capacity a pair a thread, at most four
+        // workgroups a CU (then kPairsPerThread pairs a thread at a time)
+        const int64_t batches = (max_cap + kBlock - 1) / kBlock;
+        const int64_t most = int64_t(cus) * 4;
+        const uint32_t grid = uint32_t(batches < 1 ? 1 : batches < most ? batches : most);
+        apply_direct_kernel<<<grid, kBlock, 0, stream>>>(p.idx[0], p.val[0], p.count[0], p.cap[0],
+                                                         d, x, ctl);
+        return hipGetLastError();
+    }
     // about sixteen workgroups per CU over all workers, so that a payload's
     // chain of dependent accesses (count, pairs, counter atomic, slot) runs
     // once or twice per workgroup: payloads are usually far shorter than

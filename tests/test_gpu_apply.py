@@ -309,3 +309,42 @@ def test_apply_many_ranges(layout):
     assert_bits_equal(got, want)
     got, _ = run_apply(p_dev, d, efs.APPLY_AVERAGE, x0, layout=layout)
     assert_bits_equal(got, oracle.accumulate(p_ref, d))
+
+
+@pytest.mark.parametrize("n", [0, 1, 1023, 1024, 1025, 16 * 1024 + 1, 2 * 1024 * 1024 + 77])
+def test_apply_sgd_one_payload(n):
+    # the single-launch update: batch edges, more batches than workgroups, an
+    # unknown workspace and its reuse with two workers in between, and the
+    # status word raised by a bad index or a truncated count and lowered again
+    d = 3 * n + 4099
+    rng = np.random.default_rng(17 + n)
+    idx = rng.permutation(d)[:n].astype(np.int32)
+    val = rng.standard_normal(n).astype(np.float32)
+    x0, _ = host_state(d, 18)
+    want, _ = oracle.update([(idx, val)], x0, 1)
+    one, two = [(dev(idx), dev(val))], [(dev(idx), dev(val)), (dev(idx[: n // 2]), dev(val[: n // 2]))]
+    want2, _ = oracle.update([(idx, val), (idx[: n // 2], val[: n // 2])], x0, 1)
+    ws = efs.new_apply_workspace(two, d, DEV)
+    ws.copy_(torch.randint(0, 256, ws.shape, dtype=torch.uint8, device=DEV))
+    say("apply sgd one payload n=%d" % n)
+    for rep in range(3):
+        got, _ = run_apply(one, d, efs.APPLY_SGD, x0, ws=ws)
+        assert_bits_equal(got, want)
+        assert efs.sparse_status(ws) == 0
+        got, _ = run_apply(two, d, efs.APPLY_SGD, x0, ws=ws)
+        assert_bits_equal(got, want2)
+    if n == 0:
+        return
+    ctr = efs.new_counter(DEV)
+    ctr[0] = n + 1
+    got, _ = run_apply([one[0] + (ctr,)], d, efs.APPLY_SGD, x0, ws=ws)
+    assert_bits_equal(got, want)
+    assert efs.sparse_status(ws) == efs.SPARSE_TRUNCATED
+    bad = idx.copy()
+    bad[-1] = d
+    want, _ = oracle.update([(idx[:-1], val[:-1])], x0, 1)
+    got, _ = run_apply([(dev(bad), dev(val))], d, efs.APPLY_SGD, x0, ws=ws)
+    assert_bits_equal(got, want)
+    assert efs.sparse_status(ws) == efs.SPARSE_BAD_INDEX
+    got, _ = run_apply([(one[0][0][:1], one[0][1][:1])], d, efs.APPLY_SGD, x0, ws=ws)
+    assert efs.sparse_status(ws) == 0
