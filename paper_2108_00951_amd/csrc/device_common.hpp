@@ -7,6 +7,9 @@
 namespace efs {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+// the same at any 4-byte aligned address (one 16-byte access all the same:
+// the hardware asks for dword alignment only)
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int kBlock = 256;              // threads per workgroup (4 waves)
 constexpr int kWave = 64;

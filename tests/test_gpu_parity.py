@@ -753,3 +753,63 @@ def test_sticky_last_error():
     efs.ht_compress(g, g.clone(), 0.1, 1e-3, idx, val, ctr)       # a good call after it
     assert lib.efs_last_error() == efs.EFS_EINVAL                # sticky until read
     assert lib.efs_last_error() == efs.EFS_OK
+
+
+@pytest.mark.parametrize("shift_g,shift_e", [(0, 0), (1, 1), (0, 3), (2, 0), (31, 31)])
+@pytest.mark.parametrize("d", [1, 33, 4096, 4097, 8192, 16_415, 524_289])
+def test_topk_views_at_any_alignment(d, shift_g, shift_e):
+    # g and e as views at their own offsets into a buffer: partial first and
+    # last tiles, three calls on one workspace (radix path, then brackets),
+    # nothing written outside e's own elements
+    k = max(1, d // 50)
+    ws = efs.new_topk_workspace(d, k, DEV)
+    idx = torch.empty(k, dtype=torch.int32, device=DEV)
+    val = torch.empty(k, dtype=torch.float32, device=DEV)
+    buf = torch.full((d + 64,), 7.0, dtype=torch.float32, device=DEV)
+    e = buf[shift_e:shift_e + d]
+    e.zero_()
+    ref = np.zeros(d, np.float32)
+    for t in range(3):
+        g_host = synth.small_gradient(4000 + t, d)
+        gbuf = torch.empty(d + 64, dtype=torch.float32, device=DEV)
+        gbuf[shift_g:shift_g + d].copy_(torch.from_numpy(g_host))
+        efs.topk_compress(gbuf[shift_g:shift_g + d], e, LR, k, idx, val, ws)
+        ri, rv, ref = oracle.topk(g_host, ref, LR, k)
+        assert_payload_equal(idx.cpu().numpy(), val.cpu().numpy(), ri, rv, "d=%d t=%d" % (d, t))
+        assert_bits_equal(e.cpu().numpy(), ref, "d=%d t=%d" % (d, t))
+    assert bool((buf[:shift_e] == 7.0).all()) and bool((buf[shift_e + d:] == 7.0).all())
+
+
+@pytest.mark.parametrize("ties", [100, 128, 129, 512, 513, 2048, 2049, 16_384, 16_385, 60_000])
+@pytest.mark.parametrize("at_zero", [False, True])
+def test_topk_threshold_bin_sizes(ties, at_zero):
+    # `ties` coordinates share the threshold's key and half of them are kept:
+    # each way the threshold's bin is ranked (in registers, by histogram, by
+    # index select, by the ordered sweep), on the radix path and from the
+    # bracket, with larger keys before and behind them and, in the bin itself,
+    # a few keys just above the tied one
+    d = 150_001
+    rng = np.random.default_rng(ties)
+    base = np.float32(0.0 if at_zero else 1.0)
+    g = np.zeros(d, np.float32)
+    if not at_zero:
+        g[:] = (rng.random(d) * 0.5).astype(np.float32)
+    at = rng.permutation(d)
+    g[at[:ties]] = base
+    near = at[ties:ties + 9]
+    g[near] = np.nextafter(base, np.float32(2.0))
+    big = at[ties + 9:ties + 1009]
+    g[big] = (2.0 + rng.random(1000)).astype(np.float32)
+    if at_zero:
+        g[at[ties + 1009:]] = -3.0   # every other coordinate is sent
+    k = int((np.abs(g) > base).sum()) + ties // 2
+    st = TopkState(d, k)
+    zero = np.zeros(d, np.float32)
+    want = None
+    for t in range(3):
+        st.e.zero_()
+        efs.topk_compress(to_dev(g), st.e, 1.0, k, st.idx[:k], st.val[:k], st.ws)
+        ri, rv, re = oracle.topk(g, zero, np.float32(1.0), k) if want is None else want
+        want = (ri, rv, re)
+        assert_payload_equal(st.idx[:k].cpu().numpy(), st.val[:k].cpu().numpy(), ri, rv, "call %d" % t)
+        assert_bits_equal(st.e.cpu().numpy(), re, "call %d" % t)
