@@ -4,36 +4,37 @@
 // of them: the largest keys (31-bit patterns of |p|), equal keys to the
 // lower index, exactly as the flat Top-k ranks them.
 //
-// Work is cut into tiles: the 4096-element blocks of the vector, clipped to
-// each segment, so every tile belongs to one segment and every whole tile is
-// 16-byte aligned.  The two sweeps take short slices of consecutive tiles in
-// turn across the vector (longer ones with many segments).  Five launches
-// (six above 2048 segments, where the reset takes two):
+// Segments of more than kWgSegMax elements are cut into tiles, the 4096-element
+// blocks of the vector clipped to the segment, so every whole tile is 16-byte
+// aligned.  The two sweeps take short slices of consecutive tiles in turn
+// across the vector (longer ones with many segments).  Shorter segments have
+// no tiles: a workgroup or a wave selects each whole.  Five launches (six
+// above 2048 segments, where the reset takes two):
 //
 //   reset    one workgroup checks the layout and forms the per-segment
 //            tables (tile ranges, payload offsets, candidate regions, the
-//            bracket); the others zero the per-segment histograms (a light
-//            segment, below, only its bracket histogram).
-//   pass1    p = e + lr*g written into e (12 B/element, streamed with the
-//            non-temporal hint); LDS histogram of key
-//            bits 30..18 (8192 bins) per segment, flushed (non-zero bins) to
-//            the segment's global histogram, except for a light segment (a
-//            bracket and at most kLightTiles tiles).  A segment within one
-//            tile is selected right there.  With a bracket [lo, hi] around the
-//            segment's threshold predicted from its last three calls on this
-//            workspace (error feedback moves it little and smoothly; the
-//            bracket reaches 2^wl keys below the prediction and 2^wh above,
-//            each 2^12..2^19, adapted per segment), keys above hi go straight
-//            to the payload, keys inside it to the candidates and to a
-//            1024-bin histogram of the bracket.
-//   select1  one workgroup per segment: when pass1 had a bracket and its
-//            counts prove the k-th key inside it, the bracket bin da holding
-//            it, and pass2's work items for the segment.  Otherwise the digit
-//            D1 holding the k-th key (for a light segment from a histogram
-//            select1 forms from its elements) and the mode: none (k = 0), all
-//            (k = size), candidates (the keys in D1 fit the segment's
-//            candidate region) or scan (they do not: a large set of equal or
-//            nearly equal magnitudes).
+//            bracket); the others zero the histograms of the segments with
+//            tiles.
+//   pass1    the segments with tiles: p = e + lr*g written into e (12
+//            B/element, streamed with the non-temporal hint); LDS histogram
+//            of key bits 30..18 (8192 bins) per segment, flushed (non-zero
+//            bins) to the segment's global histogram.  With a bracket
+//            [lo, hi] around the segment's threshold predicted from its last
+//            three calls on this workspace (error feedback moves it little and
+//            smoothly; the bracket reaches 2^wl keys below the prediction and
+//            2^wh above, each 2^12..2^19, adapted per segment), keys above hi
+//            go straight to the payload, keys inside it to the candidates and
+//            to a 1024-bin histogram of the bracket.
+//   select   the segments without tiles, step and selection in one read of g
+//            and e; those a workgroup selects list the keys not below their
+//            bracket's lower end while they are formed.  And, one workgroup
+//            per segment with tiles: when pass1 had a bracket and its counts
+//            prove the k-th key inside it, the bracket bin da holding it, and
+//            pass2's work items for the segment.  Otherwise the digit D1
+//            holding the k-th key and the mode: none (k = 0), all (k = size),
+//            candidates (the keys in D1 fit the segment's candidate region) or
+//            scan (they do not: a large set of equal or nearly equal
+//            magnitudes).
 //   pass2    radix path, a read of p (4 B/element): keys above D1 go to the
 //            payload and their e to +0 (mode all: every key); keys in D1 are
 //            appended to the candidate region and histogrammed by bits 17..8.
@@ -77,20 +78,17 @@ constexpr int64_t kCandExtra = 4096;
 
 enum : uint32_t {
     kModeNone = 0, kModeAll = 1, kModeCand = 2, kModeScan = 3, kModeFast = 4,
-    kModeDone = 5  // a segment within one tile, selected entirely in pass1
+    kModeDone = 5,  // a segment without tiles, selected whole
+    kModeHit = 6    // the same, from its bracket
 };
 
-// SegState::bracket: 0 none, kBracketFull a bracket with the digit-1
-// histogram kept as well, kBracketLight a bracket alone.  A segment of at
-// most kLightTiles tiles with a bracket is light: pass1 keeps no digit-1
-// histogram for it and the reset zeroes only its 4 KiB bracket histogram
-// (32 KiB less per layer to clear each call, the larger part of the reset
-// with thousands of layers, and no histogram flush in pass1).  When its
-// bracket misses, select1 forms the digit-1 histogram from the segment's
-// elements (at most kLightTiles * kTile of them, one sweep by the
-// segment's workgroup) and the radix path follows as for any other miss.
-constexpr uint32_t kBracketFull = 1u, kBracketLight = 2u;
-constexpr uint32_t kLightTiles = 4;
+// Segments of at most kWgSegMax elements are selected in pass 1 by one
+// workgroup: no histogram in memory, bracket or later launch.  Such a segment
+// is one tile wherever it starts.  With only the segments inside one
+// 4096-element block selected so, a step over the 2e4 layers of 2.56e7 elements
+// took 293 us (a fifth of them cut in two by a block boundary), 159 so, and
+// over 161 layers 117.
+constexpr int64_t kWgSegMax = 16384;
 
 // log2 of how far the bracket reaches below and above the predicted
 // threshold, each adapted per segment between these (2^19 keys are 3-6 % of
@@ -116,9 +114,15 @@ constexpr int64_t kSliceTilesMax = 4;
 // once or a few times.
 constexpr int32_t kSearchTwoRounds = kWave * kWave;
 constexpr int64_t kSliceTilesMaxMany = 64;
-// A one-tile segment with k at most kSmallK takes k block-wide maxima
-// instead of the three-level radix select (k barriers instead of about 17).
+// One wave selects a segment with k at most kSmallK by k wave-wide maxima.
 constexpr int64_t kSmallK = 8;
+// One workgroup selects a segment with k at most kMaximaK among the elements
+// not below the k-th largest of its threads' maxima (at least k of them, and
+// hardly more), ranked against one another; a larger k by a radix select on
+// the keys, which takes about 17 barriers and three passes over the registers.
+constexpr int64_t kMaximaK = 48;
+constexpr uint32_t kWgList = 2048;             // elements listed, at most
+constexpr uint32_t kWgRank = 384;              // ... ranked against one another; more by a radix select
 // Flags of groups of consecutive tiles (2^sweep_shift tiles a group, at most
 // kSweepGroups groups): select1 marks the groups of the segments that need
 // pass2's tile sweep, and pass2 skips every slice whose groups are unmarked.
@@ -204,10 +208,29 @@ __device__ __forceinline__ bool hint_usable(const SegHint &h) {
     return h.magic == kHintMagic && h.key <= 0x7fffffffu && h.prev <= 0x7fffffffu &&
            h.prev2 <= 0x7fffffffu && widths_ok(h.width);
 }
-__device__ __forceinline__ uint32_t bracket_kind(uint32_t ntiles, int64_t keff, int64_t size,
-                                                 const SegHint &h) {
-    if (!(ntiles > 1u && keff > 0 && keff < size && hint_usable(h))) return 0u;
-    return ntiles <= kLightTiles ? kBracketLight : kBracketFull;
+__device__ __forceinline__ bool forms_bracket(uint32_t ntiles, int64_t keff, int64_t size,
+                                              const SegHint &h) {
+    return ntiles > 0u && keff > 0 && keff < size && hint_usable(h);
+}
+
+// The bracket of a usable hint: around the last threshold plus the last step
+// (capped), since error feedback makes thresholds drift smoothly from call to
+// call.
+struct Bracket {
+    uint32_t lo, hi;
+};
+__device__ __forceinline__ Bracket bracket_of(const SegHint &h) {
+    const int64_t last = int64_t(h.key) - int64_t(h.prev);
+    const int64_t before = int64_t(h.prev) - int64_t(h.prev2);
+    const int64_t al = last < 0 ? -last : last, ab = before < 0 ? -before : before;
+    const bool steady = (last >= 0) == (before >= 0) && 2 * ab >= al && 2 * al >= ab;
+    const int64_t cap = steady ? kMaxStep : kMaxStepUnsure;
+    const int64_t step = max(-cap, min(cap, last));
+    const int64_t pred = max(int64_t(0), min(int64_t(0x7fffffff), int64_t(h.key) + step));
+    Bracket b;
+    b.lo = uint32_t(max(int64_t(0), pred - (int64_t(1) << width_lo(h.width))));
+    b.hi = uint32_t(min(pred + (int64_t(1) << width_hi(h.width)) - 1, int64_t(0x7fffffff)));
+    return b;
 }
 
 struct SegWs {
@@ -443,12 +466,14 @@ __device__ __forceinline__ bool slice_meets(int j, uint32_t lo, uint32_t hi) {
     return uint32_t(j) * (4u * kBlock) < hi && uint32_t(j + 1) * (4u * kBlock) > lo;
 }
 
-// Tiles of a segment: the 4096-element blocks it overlaps.
+// Tiles of a segment: none when it is selected whole (at most kWgSegMax
+// elements), else the 4096-element blocks it overlaps (at least five).
 __host__ __device__ __forceinline__ int64_t segment_tiles(int64_t off, int64_t size) {
-    return size == 0 ? 0 : ((off + size - 1) / kTile) - (off / kTile) + 1;
+    return size <= kWgSegMax ? 0 : ((off + size - 1) / kTile) - (off / kTile) + 1;
 }
 
-// Tile t of segment `inf`: the block start and the element range [lo, hi).
+// Tile t of segment `inf`: the block start and the element
+// range [lo, hi).
 struct TileRange {
     int64_t block0, lo, hi;
 };
@@ -537,7 +562,7 @@ __device__ __forceinline__ Sums seg_sums(const SegIn &in, int32_t s, int32_t nse
     if (size >= 0 && in.k >= 0) {
         const int64_t keff = in.k < size ? in.k : size;
         const uint32_t nt = uint32_t(segment_tiles(in.lo, size));
-        const int64_t ccap = (nt > 1u && keff > 0 && keff < size) ? kCandPerK * keff + kCandExtra : 0;
+        const int64_t ccap = (nt > 0u && keff > 0 && keff < size) ? kCandPerK * keff + kCandExtra : 0;
         // bracket path: the pairs above the bracket (at most k) and the
         // candidates (at most ccap), kChunk per work item
         const int64_t wmax = ccap > 0 ? (keff + kChunk - 1) / kChunk + (ccap + kChunk - 1) / kChunk : 0;
@@ -576,20 +601,12 @@ __device__ __forceinline__ Sums reset_chunk(const SegWs &ws, const SegIn &in, in
         ws.info[s] = inf;
         ws.tile_prefix[s] = uint32_t(carry.t + ex.t);
         SegState z = {};
-        const uint32_t kind = bracket_kind(nt, keff, size, h);
-        if (kind != 0u) {
-            // last threshold plus the last step (capped): error feedback
-            // makes thresholds drift smoothly from call to call
-            const int64_t last = int64_t(h.key) - int64_t(h.prev);
-            const int64_t before = int64_t(h.prev) - int64_t(h.prev2);
-            const int64_t al = last < 0 ? -last : last, ab = before < 0 ? -before : before;
-            const bool steady = (last >= 0) == (before >= 0) && 2 * ab >= al && 2 * al >= ab;
-            const int64_t cap = steady ? kMaxStep : kMaxStepUnsure;
-            const int64_t step = max(-cap, min(cap, last));
-            const int64_t pred = max(int64_t(0), min(int64_t(0x7fffffff), int64_t(h.key) + step));
-            z.bracket = kind;
-            z.lo = uint32_t(max(int64_t(0), pred - (int64_t(1) << width_lo(h.width))));
-            z.hi = uint32_t(min(pred + (int64_t(1) << width_hi(h.width)) - 1, int64_t(0x7fffffff)));
+        if (nt == 0u) z.mode = kModeDone;
+        if (forms_bracket(nt, keff, size, h)) {
+            const Bracket b = bracket_of(h);
+            z.bracket = 1u;
+            z.lo = b.lo;
+            z.hi = b.hi;
             // hi - lo + 1 <= 2^20 keys in kFineBins bins
             const uint32_t span_bits = 32u - uint32_t(__clz(int(z.hi - z.lo) | 1));
             z.shift = span_bits > 10u ? span_bits - 10u : 0u;
@@ -599,32 +616,20 @@ __device__ __forceinline__ Sums reset_chunk(const SegWs &ws, const SegIn &in, in
     return tot;
 }
 
-// Zeroes the sweep flags and the histograms of the layers that span more
-// than one tile (a one-tile layer is selected inside pass1), workgroup w of
-// nw: the digit-1 histogram unless the layer is light this call (the table
-// workgroup decides that from the same hint), and the bracket or digit-2
-// histogram.  An invalid layout is rejected, so what is zeroed for it does
-// not matter.
-__device__ __forceinline__ void reset_zero(const SegWs &ws, const int64_t *off,
-                                           const int64_t *kin, int32_t nseg, int32_t w,
-                                           int32_t nw) {
+// Zeroes the sweep flags and the histograms of the layers of several tiles (a
+// one-tile layer is selected inside pass1), workgroup w of nw.  An invalid
+// layout is rejected, so what is zeroed for it does not matter.
+__device__ __forceinline__ void reset_zero(const SegWs &ws, const int64_t *off, int32_t nseg,
+                                           int32_t w, int32_t nw) {
     const f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
     f32x4 *fl = reinterpret_cast<f32x4 *>(ws.sweep);
     for (int q = w * kResetBlock + threadIdx.x; q < kSweepGroups / 4; q += nw * kResetBlock)
         fl[q] = z;
     for (int32_t sg = w; sg < nseg; sg += nw) {
-        const int64_t lo = off[sg], size = off[sg + 1] - lo;
-        if (size < 0) continue;
-        const uint32_t nt = uint32_t(segment_tiles(lo, size));
-        if (nt <= 1u) continue;
-        const int64_t kk = kin[sg];
-        const int64_t keff = kk < size ? kk : size;
-        const bool light = bracket_kind(nt, keff, size, ws.hint[sg]) == kBracketLight;
+        if (off[sg + 1] - off[sg] <= kWgSegMax) continue;
+        f32x4 *h1 = reinterpret_cast<f32x4 *>(ws.hist1 + int64_t(sg) * kDigit1);
         f32x4 *h2 = reinterpret_cast<f32x4 *>(ws.hist2 + int64_t(sg) * kDigit2);
-        if (!light) {
-            f32x4 *h1 = reinterpret_cast<f32x4 *>(ws.hist1 + int64_t(sg) * kDigit1);
-            for (int q = threadIdx.x; q < kDigit1 / 4; q += kResetBlock) h1[q] = z;
-        }
+        for (int q = threadIdx.x; q < kDigit1 / 4; q += kResetBlock) h1[q] = z;
         for (int q = threadIdx.x; q < kDigit2 / 4; q += kResetBlock) h2[q] = z;
     }
 }
@@ -656,7 +661,7 @@ __global__ __launch_bounds__(kResetBlock) void seg_reset_kernel(SegWs ws,
                                                                 int32_t nseg, int64_t d,
                                                                 int64_t k_total) {
     if (blockIdx.x > 0) {
-        reset_zero(ws, off, kin, nseg, int32_t(blockIdx.x) - 1, int32_t(gridDim.x) - 1);
+        reset_zero(ws, off, nseg, int32_t(blockIdx.x) - 1, int32_t(gridDim.x) - 1);
         return;
     }
     __shared__ Sums s_wave[kResetWaves];
@@ -701,8 +706,7 @@ __global__ __launch_bounds__(kResetBlock) void seg_reset_sums_kernel(SegWs ws,
                                                                      int32_t nseg, int64_t d,
                                                                      int32_t nchunks) {
     if (int32_t(blockIdx.x) >= nchunks) {
-        reset_zero(ws, off, kin, nseg, int32_t(blockIdx.x) - nchunks,
-                   int32_t(gridDim.x) - nchunks);
+        reset_zero(ws, off, nseg, int32_t(blockIdx.x) - nchunks, int32_t(gridDim.x) - nchunks);
         return;
     }
     __shared__ Sums s_wave[kResetWaves];
@@ -950,110 +954,362 @@ __device__ __forceinline__ void stage_tile(Stage &sg, uint32_t &efill, uint32_t 
     __syncthreads();
 }
 
-// A segment that lies within one tile is selected here, by the workgroup
-// holding it: for a small k, k rounds of a block-wide maximum of (key, lower
-// index first); otherwise a radix select on the keys of its elements (bits
-// 30..20, 19..10, 9..0, histograms in LDS), the keys equal to the threshold
-// kept in index order.  The pairs are written to the segment's payload
-// region and e cleared at them (e already holds p).  Element (j, c) of a
-// thread is index block0 + tile_off(j, c), block0 being the segment's first
-// element.  `hist` is 2048 words of zeroed LDS, zeroed again on return.
-// Called by every thread of the workgroup.
-__device__ void select_in_tile(const float (&p)[kVecPerThread][4], uint32_t valid,
-                               int64_t block0, const SegInfo &inf, uint32_t *hist,
-                               uint32_t *s_wave, uint32_t *s_out, int32_t *idx, float *val,
-                               float *e) {
-    const int tid = threadIdx.x;
-    // slices j >= jn hold none of the segment (its elements start at block0)
-    const int jn = int((uint32_t(inf.size) + 4u * kBlock - 1u) / (4u * kBlock));
-    uint32_t key[kVecPerThread][4];
+// LDS of a workgroup selecting a segment in registers (beside 2048 words of
+// zeroed histogram, left zero).
+struct WgShared {
+    uint32_t best[kBlock];      // a thread's largest key + 1 (0: it has no element)
+    uint2 item[kWgList];        // (bits of p, offset in the segment)
+    uint32_t wave[kWaves];
+    uint32_t out[3];
+    uint32_t count, above, cut, T;
+};
+
+// The k-th largest of the threads' `best` (0 for a thread without elements),
+// as a key: at least k elements are not below it.  0 when fewer than k
+// threads hold elements.  Also clears sh.count.  Called after a barrier that
+// follows the last use of sh; two barriers.
+__device__ __forceinline__ uint32_t maxima_cut(WgShared &sh, uint32_t best, uint32_t k) {
+    const uint32_t tid = threadIdx.x;
+    sh.best[tid] = best;
+    if (tid == 0) {
+        sh.count = 0u;
+        sh.cut = 0u;
+    }
+    __syncthreads();
+    uint32_t rank = 0u;
+    const uint4 *b4 = reinterpret_cast<const uint4 *>(sh.best);
+#pragma unroll 8
+    for (uint32_t q = 0; q < uint32_t(kBlock / 4); ++q) {
+        const uint4 v = b4[q];
+        rank += (v.x > best || (v.x == best && 4u * q < tid)) ? 1u : 0u;
+        rank += (v.y > best || (v.y == best && 4u * q + 1u < tid)) ? 1u : 0u;
+        rank += (v.z > best || (v.z == best && 4u * q + 2u < tid)) ? 1u : 0u;
+        rank += (v.w > best || (v.w == best && 4u * q + 3u < tid)) ? 1u : 0u;
+    }
+    if (rank == k - 1u && best != 0u) sh.cut = best - 1u;
+    __syncthreads();
+    return sh.cut;
+}
+
+// Lists a thread's elements of `mine` (bit 4 * j + c, offset
+// base + (j * kBlock + tid) * 4 + c).
+__device__ __forceinline__ void list_mine(WgShared &sh, uint32_t mine, uint32_t base,
+                                          const float (&p)[kVecPerThread][4]) {
+    if (mine == 0u) return;
+    uint32_t at = atomicAdd(&sh.count, uint32_t(__popc(mine)));
 #pragma unroll
     for (int j = 0; j < kVecPerThread; ++j)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) key[j][c] = magnitude_key(p[j][c]);
-    uint32_t keep = 0;
-    if (inf.k >= inf.size) {
-        keep = valid;
-    } else if (inf.k <= kSmallK) {
-        // k rounds of a block-wide maximum over the elements not yet kept,
-        // of (key, then the lower index): one barrier a round
-        __shared__ uint64_t s_best[2][kWaves];
-        const int lane = tid & (kWave - 1);
-        const int wave = tid / kWave;
-#pragma unroll 1
-        for (int r = 0; r < int(inf.k); ++r) {
-            // this thread's elements in (j, c) order are in index order, so
-            // the first strictly larger key is its best
-            const uint32_t open = valid & ~keep;
-            uint64_t best = 0;
-            if (__any(open != 0u)) {  // waves past the segment's end skip this
-                uint32_t bk = 0, bs = 32;
-#pragma unroll
-                for (int j = 0; j < kVecPerThread; ++j)
-                    if (j < jn)
-#pragma unroll
-                        for (int c = 0; c < 4; ++c)
-                            if (((open >> (4 * j + c)) & 1u) && (bs == 32 || key[j][c] > bk)) {
-                                bk = key[j][c];
-                                bs = uint32_t(4 * j + c);
-                            }
-                if (bs != 32) {
-                    const uint32_t pos =
-                        ((bs >> 2) * uint32_t(kBlock) + uint32_t(tid)) * 4u + (bs & 3u);
-                    best = (uint64_t(bk) << 32) | (0xffffffffu - pos);
-                }
-                best = wave_max_u64(best);
+        for (int c = 0; c < 4; ++c)
+            if ((mine >> (4 * j + c)) & 1u) {
+                if (at < kWgList)
+                    sh.item[at] = make_uint2(__float_as_uint(p[j][c]), base + tile_off(j, c));
+                ++at;
             }
-            if (lane == 0) s_best[r & 1][wave] = best;
-            __syncthreads();
-            uint64_t all = s_best[r & 1][0];
-#pragma unroll
-            for (int q = 1; q < kWaves; ++q) all = s_best[r & 1][q] > all ? s_best[r & 1][q] : all;
-            // every valid element scores above 0, and k < size of them exist
-            const uint32_t pos = 0xffffffffu - uint32_t(all);
-            const uint32_t quad = pos >> 2;
-            if (int(quad % uint32_t(kBlock)) == tid)
-                keep |= 1u << (4 * (quad / uint32_t(kBlock)) + (pos & 3u));
+}
+
+// Of the n listed elements (k <= n <= kWgList; larger key first, then lower
+// index) the first k go to the payload, e cleared at them (their p was written
+// before the caller's last barrier), and sh.T gets the k-th key.  A few are
+// ranked against one another, more by a radix select on the key (bits 30..20,
+// 19..10, 9..0) and, when only some of the keys equal to the threshold are
+// kept, on the offset (bits 13..3, 2..0).  `hist` as for select_in_wg.
+__device__ __forceinline__ void rank_listed(WgShared &sh, uint32_t n, uint32_t k,
+                                            const SegInfo &inf, float *es, uint32_t *hist,
+                                            int32_t *__restrict__ idx, float *__restrict__ val) {
+    const uint32_t tid = threadIdx.x;
+    auto send = [&](uint32_t r, const uint2 &it) {
+        idx[inf.kout + r] = int32_t(inf.off + it.y);
+        val[inf.kout + r] = __uint_as_float(it.x);
+        es[it.y] = 0.0f;
+    };
+    if (n <= kWgRank) {
+        for (uint32_t i = tid; i < n; i += kBlock) {
+            const uint2 it = sh.item[i];
+            const uint32_t key = it.x & 0x7fffffffu;
+            uint32_t r = 0u;
+#pragma unroll 8
+            for (uint32_t q = 0; q < n; ++q) {
+                const uint2 v = sh.item[q];
+                const uint32_t vk = v.x & 0x7fffffffu;
+                r += (vk > key || (vk == key && v.y < it.y)) ? 1u : 0u;
+            }
+            if (r < k) send(r, it);
+            if (r == k - 1u) sh.T = key;
         }
-    } else if (inf.k > 0) {
-        uint32_t need = uint32_t(inf.k), prefix = 0;
+        return;
+    }
+    uint32_t need = k, prefix = 0, ties = 0;
 #pragma unroll 1
-        for (int level = 0; level < 3; ++level) {
-            const int shift = 20 - 10 * level;
-            const uint32_t mask = level == 0 ? 2047u : 1023u;
+    for (int level = 0; level < 3; ++level) {
+        const int shift = 20 - 10 * level;
+        for (uint32_t i = tid; i < n; i += kBlock) {
+            const uint32_t key = sh.item[i].x & 0x7fffffffu;
+            if (level == 0 || (key >> (shift + 10)) == prefix)
+                atomicAdd(&hist[(key >> shift) & (level == 0 ? 2047u : 1023u)], 1u);
+        }
+        __syncthreads();
+        pick_bin<2048, true>(hist, need, sh.wave, sh.out);
+        prefix = (prefix << (level == 0 ? 11 : 10)) | sh.out[0];
+        need -= sh.out[1];
+        ties = sh.out[2];
+        for (int b = tid; b < 2048; b += kBlock) hist[b] = 0u;
+        __syncthreads();
+    }
+    const uint32_t T = prefix;
+    uint32_t omax = 0xffffffffu;   // ties at offsets up to this are kept
+    if (need < ties) {
+        uint32_t first = 0;
+#pragma unroll 1
+        for (int level = 0; level < 2; ++level) {
+            for (uint32_t i = tid; i < n; i += kBlock) {
+                const uint2 it = sh.item[i];
+                if ((it.x & 0x7fffffffu) != T || (level > 0 && (it.y >> 3) != first)) continue;
+                atomicAdd(&hist[level == 0 ? it.y >> 3 : it.y & 7u], 1u);
+            }
+            __syncthreads();
+            pick_bin<2048, false>(hist, need, sh.wave, sh.out);
+            first = level == 0 ? sh.out[0] : (first << 3) | sh.out[0];
+            need -= sh.out[1];
+            for (int b = tid; b < 2048; b += kBlock) hist[b] = 0u;
+            __syncthreads();
+        }
+        omax = first;
+    }
+    if (tid == 0) {
+        sh.count = 0u;
+        sh.T = T;
+    }
+    __syncthreads();
+    for (uint32_t i = tid; i < n; i += kBlock) {
+        const uint2 it = sh.item[i];
+        const uint32_t key = it.x & 0x7fffffffu;
+        if (key > T || (key == T && it.y <= omax)) send(atomicAdd(&sh.count, 1u), it);
+    }
+}
+static_assert(kWgSegMax <= 1 << 14, "an offset has 14 bits");
+
+// Loads p = e + lr*g (kStep) or e of the 4096 elements from offset `base` of
+// a segment of `size` for this thread (element (j, c) at base + tile_off), in
+// 16-byte accesses at whatever alignment the segment has; `valid` marks those
+// inside it.
+template <bool kStep>
+__device__ __forceinline__ void wg_load(const float *__restrict__ gs, const float *es,
+                                        float lr, uint32_t base, uint32_t size,
+                                        float (&p)[kVecPerThread][4], uint32_t &valid) {
+    f32x4 gv[kVecPerThread], ev[kVecPerThread];
+    valid = 0u;
+#pragma unroll
+    for (int j = 0; j < kVecPerThread; ++j) {
+        const f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
+        gv[j] = z;
+        ev[j] = z;
+        if (base + uint32_t(j) * 4u * kBlock >= size) continue;   // the same in every thread
+        const uint32_t o = base + tile_off(j, 0);
+        if (o + 4u <= size) {
+            if (kStep) gv[j] = __builtin_nontemporal_load(reinterpret_cast<const f32x4u *>(gs + o));
+            ev[j] = *reinterpret_cast<const f32x4u *>(es + o);
+            valid |= 0xfu << (4 * j);
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (o + uint32_t(c) < size) {
+                    if (kStep) gv[j][c] = gs[o + c];
+                    ev[j][c] = es[o + c];
+                    valid |= 1u << (4 * j + c);
+                }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < kVecPerThread; ++j)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            p[j][c] = kStep ? ef_accumulate(ev[j][c], lr, gv[j][c]) : ev[j][c];
+}
+
+// Writes p, +0 at the elements of `keep`, for the elements of `valid`.
+__device__ __forceinline__ void wg_store(float *es, uint32_t base, uint32_t valid, uint32_t keep,
+                                         const float (&p)[kVecPerThread][4]) {
+#pragma unroll
+    for (int j = 0; j < kVecPerThread; ++j) {
+        const uint32_t here = (valid >> (4 * j)) & 0xfu;
+        const uint32_t o = base + tile_off(j, 0);
+        f32x4 v;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] = ((keep >> (4 * j + c)) & 1u) ? 0.0f : p[j][c];
+        if (here == 0xfu) {
+            *reinterpret_cast<f32x4u *>(es + o) = v;
+        } else if (here != 0u) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if ((here >> c) & 1u) es[o + c] = v[c];
+        }
+    }
+}
+
+// Elements of this thread (bits as `valid`) whose key is at least `cut`.
+__device__ __forceinline__ uint32_t not_below(uint32_t valid, uint32_t cut,
+                                              const float (&p)[kVecPerThread][4]) {
+    uint32_t m = 0u;
+#pragma unroll
+    for (int j = 0; j < kVecPerThread; ++j)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            m |= uint32_t(magnitude_key(p[j][c]) >= cut) << (4 * j + c);
+    return m & valid;
+}
+
+// This thread's largest key + 1 over the elements of `valid` (0: none).
+__device__ __forceinline__ uint32_t thread_best(uint32_t valid,
+                                                const float (&p)[kVecPerThread][4]) {
+    uint32_t best = 0u;
+#pragma unroll
+    for (int j = 0; j < kVecPerThread; ++j)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if ((valid >> (4 * j + c)) & 1u) best = max(best, magnitude_key(p[j][c]) + 1u);
+    return best;
+}
+
+// The error-feedback step and the selection of a segment of at most kWgSegMax
+// elements by one workgroup, 4096 at a time: p goes to e at once and is read
+// back (from the cache: each thread its own elements) where the selection
+// needs it again.  (Holding p in registers took 121 VGPRs for 4096 elements, 57
+// so: twice the workgroups a CU, which hide one another's round trips.)  With
+// a hint the elements not below its bracket are listed on the way (`listed`
+// of them), and the list selects when it holds the k-th; without, or when it
+// does not, the list comes from the threads' maxima, or a radix select reads e
+// three times.  Returns the threshold, or kNoThreshold when nothing or
+// everything is kept; `inside` says whether the bracket held it.  `hist` is
+// 2048 words of zeroed LDS, zeroed again on return.  Called by every thread of the
+// workgroup, after a barrier that follows the last use of sh.
+constexpr uint32_t kNoThreshold = 0xffffffffu;
+
+__device__ __forceinline__ uint32_t select_in_wg(const float *__restrict__ g, float *e, float lr,
+                                                 int32_t *__restrict__ idx,
+                                                 float *__restrict__ val, const SegInfo &inf,
+                                                 bool hinted, const Bracket &br, uint32_t &listed,
+                                                 bool &inside, uint32_t *hist, WgShared &sh) {
+    const uint32_t tid = threadIdx.x;
+    const uint32_t size = uint32_t(inf.size);
+    const uint32_t k = uint32_t(inf.k);
+    const float *gs = g + inf.off;
+    float *es = e + inf.off;
+    const bool all = inf.k >= inf.size;
+    hinted = hinted && !all && k > 0u;
+    listed = 0u;
+    inside = false;
+    if (tid == 0) {
+        sh.count = 0u;
+        sh.above = 0u;
+    }
+    __syncthreads();
+    float p[kVecPerThread][4];
+    uint32_t valid = 0u, best = 0u;
+    // f(base): p and valid of the 4096 elements from `base` on read back
+    auto sweep = [&](auto f) {
+#pragma unroll 1
+        for (uint32_t base = 0; base < size; base += uint32_t(kTile)) {
+            wg_load<false>(gs, es, lr, base, size, p, valid);
+            f(base);
+        }
+    };
+#pragma unroll 1
+    for (uint32_t base = 0; base < size; base += uint32_t(kTile)) {
+        wg_load<true>(gs, es, lr, base, size, p, valid);
+        best = max(best, thread_best(valid, p));
+        if (all) {
 #pragma unroll
             for (int j = 0; j < kVecPerThread; ++j)
 #pragma unroll
                 for (int c = 0; c < 4; ++c)
-                    if (((valid >> (4 * j + c)) & 1u) &&
-                        (level == 0 || (key[j][c] >> (shift + 10)) == prefix))
-                        atomicAdd(&hist[(key[j][c] >> shift) & mask], 1u);
-            __syncthreads();
-            if (level == 0) pick_bin<2048, true>(hist, need, s_wave, s_out);
-            else pick_bin<1024, true>(hist, need, s_wave, s_out);
-            prefix = (prefix << (level == 0 ? 11 : 10)) | s_out[0];
-            need -= s_out[1];
-            for (int b = tid; b < 2048; b += kBlock) hist[b] = 0u;
-            __syncthreads();
+                    if ((valid >> (4 * j + c)) & 1u) {
+                        const uint32_t o = base + tile_off(j, c);
+                        idx[inf.kout + o] = int32_t(inf.off + o);
+                        val[inf.kout + o] = p[j][c];
+                    }
         }
-        const uint32_t T = prefix;  // need = keys equal to T to keep
-        uint32_t tie = 0;
+        wg_store(es, base, valid, all ? valid : 0u, p);
+        if (hinted) {
+            const uint32_t mine = not_below(valid, br.lo, p);
+            if (mine != 0u) {
+                const uint32_t above = not_below(mine, br.hi + 1u, p);
+                if (above != 0u) atomicAdd(&sh.above, uint32_t(__popc(above)));
+                list_mine(sh, mine, base, p);
+            }
+        }
+    }
+    if (all || k == 0u) return kNoThreshold;
+    __syncthreads();
+    if (hinted) {
+        const uint32_t n = sh.count;
+        listed = n;
+        inside = n >= k && sh.above <= k;
+        if (n >= k && n <= kWgList) {
+            __syncthreads();   // sh.count is read above, and rank_listed may use it
+            rank_listed(sh, n, k, inf, es, hist, idx, val);
+            __syncthreads();
+            return sh.T;
+        }
+        __syncthreads();
+    }
+    if (k <= uint32_t(kMaximaK)) {
+        const uint32_t cut = maxima_cut(sh, best, k);
+        if (best > cut)
+            sweep([&](uint32_t base) { list_mine(sh, not_below(valid, cut, p), base, p); });
+        __syncthreads();
+        const uint32_t n = sh.count;
+        __syncthreads();
+        if (n <= kWgList) {
+            rank_listed(sh, n, k, inf, es, hist, idx, val);
+            __syncthreads();
+            return sh.T;
+        }
+    }
+    uint32_t need = k, prefix = 0, ties = 0;
+#pragma unroll 1
+    for (int level = 0; level < 3; ++level) {
+        const int shift = 20 - 10 * level;
+        const uint32_t mask = level == 0 ? 2047u : 1023u;
+        sweep([&](uint32_t) {
 #pragma unroll
-        for (int j = 0; j < kVecPerThread; ++j)
+            for (int j = 0; j < kVecPerThread; ++j)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const uint32_t key = magnitude_key(p[j][c]);
+                    if (((valid >> (4 * j + c)) & 1u) &&
+                        (level == 0 || (key >> (shift + 10)) == prefix))
+                        atomicAdd(&hist[(key >> shift) & mask], 1u);
+                }
+        });
+        __syncthreads();
+        if (level == 0) pick_bin<2048, true>(hist, need, sh.wave, sh.out);
+        else pick_bin<1024, true>(hist, need, sh.wave, sh.out);
+        prefix = (prefix << (level == 0 ? 11 : 10)) | sh.out[0];
+        need -= sh.out[1];
+        ties = sh.out[2];
+        for (int b = tid; b < 2048; b += kBlock) hist[b] = 0u;
+        __syncthreads();
+    }
+    const uint32_t T = prefix;  // need = keys equal to T to keep, of ties
+    uint32_t rank = 0;          // tie ranks in index order: vector slot j, then thread, then c
+    int64_t slot0 = inf.kout;
+    sweep([&](uint32_t base) {
+        uint32_t keep = 0u;
+#pragma unroll
+        for (int j = 0; j < kVecPerThread; ++j) {
+            uint32_t tj = 0;
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 const uint32_t bit = 1u << (4 * j + c);
+                const uint32_t key = magnitude_key(p[j][c]);
                 if (!(valid & bit)) continue;
-                if (key[j][c] > T) keep |= bit;
-                else if (key[j][c] == T) tie |= bit;
+                if (key > T || (key == T && need == ties)) keep |= bit;
+                else if (key == T) tj |= 1u << c;
             }
-        // tie ranks in index order: vector slot j, then thread, then c
-        uint32_t rank = 0;
-#pragma unroll
-        for (int j = 0; j < kVecPerThread; ++j) {
-            const uint32_t tj = (tie >> (4 * j)) & 0xfu;
+            if (need == ties) continue;
             uint32_t slot_total;
-            uint32_t r = rank + block_prefix_small(uint32_t(__popc(tj)), s_wave, slot_total);
+            uint32_t r = rank + block_prefix_small(uint32_t(__popc(tj)), sh.wave, slot_total);
 #pragma unroll
             for (int c = 0; c < 4; ++c)
                 if ((tj >> c) & 1u) {
@@ -1062,27 +1318,27 @@ __device__ void select_in_tile(const float (&p)[kVecPerThread][4], uint32_t vali
                 }
             rank += slot_total;
         }
-    }
-    uint32_t total;
-    int64_t slot = inf.kout + block_prefix_small(uint32_t(__popc(keep)), s_wave, total);
+        uint32_t total;
+        int64_t slot = slot0 + block_prefix_small(uint32_t(__popc(keep)), sh.wave, total);
+        slot0 += total;
 #pragma unroll
-    for (int j = 0; j < kVecPerThread; ++j)
+        for (int j = 0; j < kVecPerThread; ++j)
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-            if ((keep >> (4 * j + c)) & 1u) {
-                const int64_t i = tile_elem(block0, j, c);
-                idx[slot] = int32_t(i);
-                val[slot] = p[j][c];
-                e[i] = 0.0f;
-                ++slot;
-            }
+            for (int c = 0; c < 4; ++c)
+                if ((keep >> (4 * j + c)) & 1u) {
+                    const uint32_t o = base + tile_off(j, c);
+                    idx[slot] = int32_t(inf.off + o);
+                    val[slot] = p[j][c];
+                    es[o] = 0.0f;
+                    ++slot;
+                }
+    });
+    return T;
 }
 
-// Small one-tile segments (at most kWaveLayerMax elements, k <= kSmallK or
-// every element kept) are selected by one wave each, so that a workgroup
-// takes up to kWaves of them at once with no barrier: models with thousands
-// of tensors have mostly such layers, and one at a time each cost the
-// workgroup a memory round trip and a few barriers.
+// Small segments (at most kWaveLayerMax elements, k <= kSmallK or every
+// element kept) are selected by one wave each, kWaves of them at once with no
+// barrier: models with thousands of tensors have mostly such layers.
 constexpr int kWaveLayerMax = 16 * kWave;  // 16 elements a lane
 
 __device__ __forceinline__ bool wave_layer(int64_t size, int64_t k) {
@@ -1161,60 +1417,12 @@ __device__ __forceinline__ void select_in_wave(const float *__restrict__ g, floa
     }
 }
 
-// Segment s (holding tile t, one tile, small) and the segments after it
-// that hold tiles t + 1, t + 2, ... (below t1) and are small one-tile
-// segments as well, up to kWaves of them: wave w selects segment s + w.
-// Returns how many were taken (at least 1; the same in every thread).  No
-// barrier: each wave reads the tables of s + 1 .. s + 3 itself, one dword a
-// lane (lanes 16 (w - 1) .. 16 w - 1 hold segment s + w's SegInfo).
-__device__ __forceinline__ uint32_t wave_layers(const float *__restrict__ g,
-                                                float *__restrict__ e, float lr,
-                                                int32_t *__restrict__ idx,
-                                                float *__restrict__ val, int32_t nseg,
-                                                const SegWs &ws, int32_t s, const SegInfo &inf,
-                                                uint32_t t, uint32_t t1) {
-    constexpr int kInfoWords = sizeof(SegInfo) / 4;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave);
-    uint32_t tab = 0u;  // a segment not loaded reads as 0 tiles
-    {
-        const int w = 1 + lane / kInfoWords;
-        if (w < kWaves && s + w < nseg && t + uint32_t(w) < t1)
-            tab = reinterpret_cast<const uint32_t *>(ws.info + s + w)[lane % kInfoWords];
-    }
-    uint32_t run = 1;
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) {
-        const int b = kInfoWords * (w - 1);
-        // segments s .. s + w - 1 hold one tile each, so s + w (when it
-        // holds any tile) holds tile t + w
-        if (run == uint32_t(w) && tab_word(tab, b + 13) == 1u &&
-            wave_layer(tab_i64(tab, b + 2), tab_i64(tab, b + 6)))
-            run = uint32_t(w + 1);
-    }
-    if (uint32_t(wave) < run) {
-        if (wave == 0) {
-            select_in_wave(g, e, lr, idx, val, inf);
-        } else {
-            const int b = kInfoWords * (wave - 1);
-            SegInfo mi;
-            mi.off = tab_i64(tab, b + 0);
-            mi.size = tab_i64(tab, b + 2);
-            mi.kout = tab_i64(tab, b + 4);
-            mi.k = tab_i64(tab, b + 6);
-            select_in_wave(g, e, lr, idx, val, mi);
-        }
-    }
-    return run;
-}
-
 // Tiles [t0, t1) of pass1; every selection, count and histogram is flushed
 // before it returns (the LDS histogram is left zero).
 template <bool kAligned>
 __device__ void pass1_slice(const float *__restrict__ g, float *__restrict__ e, float lr,
                             int32_t *__restrict__ idx, float *__restrict__ val, int32_t nseg,
-                            const SegWs &ws, uint32_t t0, uint32_t t1, uint32_t *hist, Stage &sg,
-                            uint32_t *s_wave, uint32_t *s_out) {
+                            const SegWs &ws, uint32_t t0, uint32_t t1, uint32_t *hist, Stage &sg) {
     int32_t s = segment_of_tile(ws.tile_prefix, nseg, t0);
     uint32_t next = ws.tile_prefix[s + 1];
     SegInfo inf = ws.info[s];
@@ -1230,9 +1438,7 @@ __device__ void pass1_slice(const float *__restrict__ g, float *__restrict__ e, 
             if (bracket) {
                 flush_both(sg, efill, cfill, st, inf, idx, val, ws.cand, fine);
             }
-            // a one-tile or a light segment leaves the LDS histogram zero
-            if (inf.ntiles > 1 && bracket != kBracketLight)
-                flush_hist(hist, kDigit1, ws.hist1 + int64_t(s) * kDigit1);
+            flush_hist(hist, kDigit1, ws.hist1 + int64_t(s) * kDigit1);
             if (s + 1 < nseg && tab_word(tab, kTabNext) > t) {
                 // tile t (== tile_prefix[s + 1]) opens segment s + 1: the
                 // prefetched tables
@@ -1244,7 +1450,7 @@ __device__ void pass1_slice(const float *__restrict__ g, float *__restrict__ e, 
                 hi = tab_word(tab, kTabState + 2);
                 fine = Fine{ws.hist2 + int64_t(s) * kDigit2, lo, tab_word(tab, kTabState + 3)};
             } else {
-                // past empty segments
+                // past segments without tiles
                 s = segment_of_tile(ws.tile_prefix, nseg, t);
                 next = ws.tile_prefix[s + 1];
                 inf = ws.info[s];
@@ -1255,18 +1461,6 @@ __device__ void pass1_slice(const float *__restrict__ g, float *__restrict__ e, 
             }
             st = ws.st + s;
             tab = load_seg_table(ws, nseg, s + 1);
-        }
-        if (inf.ntiles == 1 && wave_layer(inf.size, inf.k)) {
-            // this and the following small one-tile segments, a wave each;
-            // the last of them becomes the current segment (no bracket, no
-            // histogram: nothing to flush when the next tile leaves it)
-            const uint32_t run = wave_layers(g, e, lr, idx, val, nseg, ws, s, inf, t, t1);
-            s += int32_t(run) - 1;
-            t += run - 1;
-            next = t + 1;
-            st = ws.st + s;
-            if (run > 1) tab = load_seg_table(ws, nseg, s + 1);
-            continue;
         }
         const TileRange r = tile_range(inf, t);
         float p[kVecPerThread][4];
@@ -1293,14 +1487,11 @@ __device__ void pass1_slice(const float *__restrict__ g, float *__restrict__ e, 
             valid = 0xffffu;
         } else {
             // a segment's first or last block: only its own elements are
-            // read and written (the rest of the block belongs to neighbours).
-            // A segment within one block is laid over the threads from its
-            // first element on, so that a small one fills few slices and
-            // waves; slices outside the elements are skipped.
-            const int64_t base = inf.ntiles == 1 ? inf.off : r.block0;
-            const uint32_t lo = uint32_t(r.lo - base), hi = uint32_t(r.hi - base);
-            const float *gb = g + base;
-            float *eb = e + base;
+            // read and written (the rest of the block belongs to
+            // neighbours); slices outside them are skipped
+            const uint32_t lo = uint32_t(r.lo - r.block0), hi = uint32_t(r.hi - r.block0);
+            const float *gb = g + r.block0;
+            float *eb = e + r.block0;
 #pragma unroll
             for (int j = 0; j < kVecPerThread; ++j) {
 #pragma unroll
@@ -1316,13 +1507,8 @@ __device__ void pass1_slice(const float *__restrict__ g, float *__restrict__ e, 
                     }
                 }
             }
-            if (inf.ntiles == 1) {
-                select_in_tile(p, valid, base, inf, hist, s_wave, s_out, idx, val, e);
-                continue;
-            }
         }
         uint32_t emit_mask = 0, cand_mask = 0;
-        const bool digits = bracket != kBracketLight;
 #pragma unroll
         for (int j = 0; j < kVecPerThread; ++j) {
             if (!__any(((valid >> (4 * j)) & 0xfu) != 0u)) continue;  // none in this wave
@@ -1331,7 +1517,7 @@ __device__ void pass1_slice(const float *__restrict__ g, float *__restrict__ e, 
                 const uint32_t bit = 1u << (4 * j + c);
                 if (!(valid & bit)) continue;
                 const uint32_t key = magnitude_key(p[j][c]);
-                if (digits) atomicAdd(&hist[key >> kShift1], 1u);
+                atomicAdd(&hist[key >> kShift1], 1u);
                 if (key > hi) emit_mask |= bit;
                 else if (key >= lo) cand_mask |= bit;
             }
@@ -1346,8 +1532,7 @@ __device__ void pass1_slice(const float *__restrict__ g, float *__restrict__ e, 
     if (bracket) {
         flush_both(sg, efill, cfill, st, inf, idx, val, ws.cand, fine);
     }
-    if (inf.ntiles > 1 && bracket != kBracketLight)
-        flush_hist(hist, kDigit1, ws.hist1 + int64_t(s) * kDigit1);
+    flush_hist(hist, kDigit1, ws.hist1 + int64_t(s) * kDigit1);
     __syncthreads();  // the next slice starts with another segment's state
 }
 
@@ -1359,14 +1544,11 @@ __global__ __launch_bounds__(kBlock, 4) void seg_pass1_kernel(const float *__res
                                                            SegWs ws, uint32_t slice) {
     __shared__ uint32_t hist[kDigit1];
     __shared__ Stage sg;
-    __shared__ uint32_t s_wave[kWaves];
-    __shared__ uint32_t s_out[3];
     if (ws.ctl->status != 0u) return;
     const uint32_t T = ws.ctl->tiles;
     for (int b = threadIdx.x; b < kDigit1; b += kBlock) hist[b] = 0u;
     for (uint32_t t0 = blockIdx.x * slice; t0 < T; t0 += gridDim.x * slice)
-        pass1_slice<kAligned>(g, e, lr, idx, val, nseg, ws, t0, min(T, t0 + slice), hist, sg,
-                              s_wave, s_out);
+        pass1_slice<kAligned>(g, e, lr, idx, val, nseg, ws, t0, min(T, t0 + slice), hist, sg);
 }
 
 // ---------------------------------------------------------------------------
@@ -1407,66 +1589,9 @@ __device__ void choose_digit1(const SegWs &ws, int32_t s, const SegInfo &inf, Se
     if (sweep) mark_sweep(ws, inf);
 }
 
-// The digit-1 histogram of a light segment whose bracket missed (pass1 kept
-// none for it), formed from its elements: e holds p everywhere in the
-// segment, since pass1 clears e only once the bracket is confirmed.  The
-// counts are at most kLightTiles * kTile, so two 16-bit counts share an LDS
-// word (16 KiB); the 8192 bins are then stored whole into the segment's
-// global histogram, which choose_digit1 reads.  One sweep of e in 16-byte
-// vectors (the few elements before the first 16-byte boundary and after the
-// last one at a time).  Called by every thread of the workgroup.
-__device__ void light_digit1(const SegWs &ws, const float *__restrict__ e, const SegInfo &inf,
-                             int32_t s, uint32_t *pack) {
-    const uint32_t tid = threadIdx.x;
-    for (uint32_t b = tid; b < uint32_t(kDigit1 / 2); b += kBlock) pack[b] = 0u;
-    __syncthreads();
-    const float *seg = e + inf.off;
-    const uint32_t n = uint32_t(inf.size);
-    // seg + h is the first 16-byte boundary at or after seg (e is 4-byte aligned)
-    const uint32_t h = min(n, uint32_t(((16u - (reinterpret_cast<uintptr_t>(seg) & 15u)) & 15u) / 4u));
-    const uint32_t nv = (n - h) / 4u;
-    const uint32_t t0 = h + 4u * nv;
-    for (uint32_t i = tid; i < h + (n - t0); i += kBlock) {
-        const uint32_t d1 = magnitude_key(seg[i < h ? i : t0 + (i - h)]) >> kShift1;
-        atomicAdd(&pack[d1 >> 1], 1u << (16u * (d1 & 1u)));
-    }
-    const f32x4 *v4 = reinterpret_cast<const f32x4 *>(seg + h);
-    constexpr uint32_t kV = 4;  // 16-byte loads per thread in flight
-    for (uint32_t base = 0; base < nv; base += kV * kBlock) {
-        f32x4 x[kV];
-#pragma unroll
-        for (uint32_t u = 0; u < kV; ++u) {
-            const uint32_t q = base + u * kBlock + tid;
-            if (q < nv) x[u] = v4[q];
-        }
-#pragma unroll
-        for (uint32_t u = 0; u < kV; ++u) {
-            if (base + u * kBlock + tid < nv) {
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const uint32_t d1 = magnitude_key(x[u][c]) >> kShift1;
-                    atomicAdd(&pack[d1 >> 1], 1u << (16u * (d1 & 1u)));
-                }
-            }
-        }
-    }
-    __syncthreads();
-    uint2 *h1 = reinterpret_cast<uint2 *>(ws.hist1 + int64_t(s) * kDigit1);
-    for (uint32_t b = tid; b < uint32_t(kDigit1 / 2); b += kBlock) {
-        const uint32_t v = pack[b];
-        h1[b] = make_uint2(v & 0xffffu, v >> 16);
-    }
-    __syncthreads();  // the workgroup reads the histogram back
-}
-
-__device__ void select1_segment(const SegWs &ws, const float *__restrict__ e, int32_t s,
-                                uint32_t *s_wave, uint32_t *s_out, uint32_t *s_pack) {
+__device__ void select1_segment(const SegWs &ws, int32_t s, uint32_t *s_wave, uint32_t *s_out) {
     const SegInfo inf = ws.info[s];
     SegState *st = ws.st + s;
-    if (inf.ntiles <= 1) {  // selected in pass1 (or empty)
-        if (threadIdx.x == 0) st->mode = kModeDone;
-        return;
-    }
     if (inf.k == 0 || inf.k == inf.size) {
         if (threadIdx.x == 0) {
             st->mode = inf.k == 0 ? kModeNone : kModeAll;
@@ -1532,18 +1657,75 @@ __device__ void select1_segment(const SegWs &ws, const float *__restrict__ e, in
             st->miss = int64_t(cur.emit) > inf.k ? 2u
                        : (int64_t(cur.emit) + cur.ccur < inf.k ? 1u : 3u);
     }
-    if (cur.bracket == kBracketLight) light_digit1(ws, e, inf, s, s_pack);
     choose_digit1(ws, s, inf, st, s_wave, s_out);
 }
 
-// One workgroup per segment (a loop over segments per workgroup serialises
-// their latencies: measured slower with thousands of segments).
-__global__ __launch_bounds__(kBlock) void seg_select1_kernel(SegWs ws, const float *__restrict__ e) {
-    __shared__ uint32_t s_wave[kWaves];
-    __shared__ uint32_t s_out[3];
-    __shared__ uint32_t s_pack[kDigit1 / 2];
+// The first `nbig` workgroups take the segments with tiles: each reads the
+// tile counts of up to kBlock of its segments b, b + nbig, ... at once and
+// works through those that have any.  The others take `group` consecutive
+// segments each and select those without tiles, which pass1 left alone: a
+// wave each where a wave can, the rest by the workgroup one after another.
+// Both kinds in one launch: the first keep few CUs busy for a few round trips.
+__global__ __launch_bounds__(kBlock) void seg_select_kernel(const float *__restrict__ g, float *e,
+                                                            float lr, int32_t *__restrict__ idx,
+                                                            float *__restrict__ val, SegWs ws,
+                                                            int32_t nseg, int32_t nbig,
+                                                            int32_t group) {
+    __shared__ uint32_t hist[2048];
+    __shared__ WgShared wsh;
+    __shared__ int32_t s_list[kBlock];
     if (ws.ctl->status != 0u) return;
-    select1_segment(ws, e, int32_t(blockIdx.x), s_wave, s_out, s_pack);
+    if (int32_t(blockIdx.x) < nbig) {
+        const int32_t per = (nseg - int32_t(blockIdx.x) + nbig - 1) / nbig;
+        for (int32_t g0 = 0; g0 < per; g0 += kBlock) {
+            const int32_t q = g0 + int32_t(threadIdx.x);
+            const int32_t s = int32_t(blockIdx.x) + q * nbig;
+            const bool work = q < per && ws.info[s].ntiles > 0u;
+            uint32_t n;
+            const uint32_t pos = block_prefix_small(work ? 1u : 0u, wsh.wave, n);
+            if (work) s_list[pos] = s;
+            __syncthreads();
+            for (uint32_t i = 0; i < n; ++i) {
+                select1_segment(ws, s_list[i], wsh.wave, wsh.out);
+                __syncthreads();   // wsh and, after the last, s_list are rewritten
+            }
+        }
+        return;
+    }
+    const int32_t s0 = (int32_t(blockIdx.x) - nbig) * group;
+    const int32_t wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave);
+    if (wave < group && s0 + wave < nseg) {
+        const SegInfo inf = ws.info[s0 + wave];
+        if (inf.size > 0 && wave_layer(inf.size, inf.k)) select_in_wave(g, e, lr, idx, val, inf);
+    }
+    for (int b = threadIdx.x; b < 2048; b += kBlock) hist[b] = 0u;
+    for (int32_t s = s0; s < min(s0 + group, nseg); ++s) {
+        const SegInfo inf = ws.info[s];
+        if (inf.size > kWgSegMax || wave_layer(inf.size, inf.k)) continue;
+        const SegHint oh = ws.hint[s];
+        const bool hinted = hint_usable(oh);
+        Bracket br = {0u, 0u};
+        if (hinted) br = bracket_of(oh);
+        __syncthreads();   // wsh and hist are free
+        uint32_t listed;
+        bool inside;
+        const uint32_t T = select_in_wg(g, e, lr, idx, val, inf, hinted, br, listed, inside, hist,
+                                        wsh);
+        if (threadIdx.x == 0 && T != kNoThreshold) {
+            // both sides wider after the threshold fell outside the bracket,
+            // the lower one narrower after a list well over k
+            const uint32_t w0 = hinted ? oh.width : make_widths(kWidthStart, kWidthStart);
+            uint32_t wl = width_lo(w0), wh = width_hi(w0);
+            if (hinted && !inside) {
+                wl = min(wl + 1u, kWidthMax);
+                wh = min(wh + 1u, kWidthMax);
+            } else if (hinted && int64_t(listed) > 2 * inf.k + 64 && wl > kWidthMin) {
+                --wl;
+            }
+            ws.hint[s] = next_hint(oh, T, make_widths(wl, wh));
+            if (inside && listed <= kWgList) ws.st[s].mode = kModeHit;
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1578,7 +1760,7 @@ __device__ void pass2_tiles(float *__restrict__ e, int32_t *__restrict__ idx,
             mode = st->mode;
             D1 = st->d1;
         }
-        if (mode == kModeNone || mode == kModeFast || mode == kModeDone) {
+        if (mode == kModeNone || mode == kModeFast) {
             t = next - 1;  // nothing to do in this segment: skip its tiles
             continue;
         }
@@ -2035,7 +2217,7 @@ __global__ __launch_bounds__(kBlock) void seg_final_kernel(float *__restrict__ e
             mode = p->mode;
             if (mode == kModeFast) listed = p->needa != 0u ? min(p->ca, p->tcur) : 0u;
         }
-        fast += mode == kModeFast ? 1u : 0u;
+        fast += mode == kModeFast || mode == kModeHit ? 1u : 0u;
         // bracket-path segments with at most kWave keys to rank go to the
         // waves (listed from the end of s_list), the rest to the workgroup
         const bool small = mode == kModeFast && listed <= uint32_t(kWave);
@@ -2113,12 +2295,17 @@ hipError_t launch_topk_segmented(const float *g, float *e, int64_t d, float lr, 
         seg_pass1_kernel<true><<<grid, kBlock, 0, stream>>>(g, e, lr, idx, val, nseg, ws, uint32_t(slice));
     else
         seg_pass1_kernel<false><<<grid, kBlock, 0, stream>>>(g, e, lr, idx, val, nseg, ws, uint32_t(slice));
-    seg_select1_kernel<<<uint32_t(nseg), kBlock, 0, stream>>>(ws, e);
+    const int64_t cus = device_cu_count();
+    // one segment a workgroup while that fills the chip at most twice over,
+    // then four
+    const int32_t nbig = int32_t(min(int64_t(nseg), 4 * cus));
+    const int32_t group = nseg <= 8 * cus ? 1 : kWaves;
+    seg_select_kernel<<<uint32_t(nbig + (nseg + group - 1) / group), kBlock, 0, stream>>>(
+        g, e, lr, idx, val, ws, nseg, nbig, group);
     if (aligned)
         seg_pass2_kernel<true><<<grid, kBlock, 0, stream>>>(e, idx, val, nseg, ws, uint32_t(slice));
     else
         seg_pass2_kernel<false><<<grid, kBlock, 0, stream>>>(e, idx, val, nseg, ws, uint32_t(slice));
-    const int64_t cus = device_cu_count();
     if (nseg > kFinalWideMin)
         seg_final_kernel<kCandLdsSmall><<<uint32_t(min(int64_t(nseg), 4 * cus)), kBlock, 0, stream>>>(
             e, idx, val, ws, nseg);

@@ -671,3 +671,44 @@ def test_segmented_randomised_ef_loops(seed):
         hits.append(efs.topk_segmented_bracket_segments(ws))
         e = re
     say("  bracket segments per step: %s" % hits)
+
+
+@pytest.mark.parametrize("kind", ["gauss", "ties", "equal"])
+@pytest.mark.parametrize("unaligned", [False, True])
+def test_segmented_single_workgroup_sizes(kind, unaligned):
+    # sizes and budgets at the edges of the ways a segment is selected whole:
+    # by a wave (1,024 elements, k = 8), from the threads' maxima (k = 48), by
+    # a radix select, from its hint's list (up to 384 and 2,048 elements), in
+    # one to four 4096-element pieces, and the first size that has tiles
+    # (16,385).  Four calls carry the error, so the later ones have hints; with
+    # ties (grid, lr = 1) equal keys are split by index
+    rng = np.random.default_rng(5100)
+    sizes, ks = [], []
+    for size in (1, 3, 255, 1023, 1024, 1025, 4095, 4096, 4097, 8193, 12_288, 16_383, 16_384, 16_385):
+        for k in (1, 8, 9, 48, 49, 300, 385, 2048, 2049, size - 1, size):
+            if 0 < k <= size:
+                sizes.append(size)
+                ks.append(k)
+    order = rng.permutation(len(sizes))
+    sizes, ks = np.array(sizes, np.int64)[order], np.array(ks, np.int64)[order]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    d, k_total = int(off[-1]), int(ks.sum())
+    ws = efs.new_topk_segmented_workspace(ks.size, k_total, DEV)
+    ws.zero_()
+    e = np.zeros(d, np.float32)
+    say("segmented single-workgroup sizes %s unaligned=%s d=%d nseg=%d" % (kind, unaligned, d, ks.size))
+    for t in range(4):
+        if kind == "gauss":
+            g = synth.small_gradient(5200 + t, d)
+        elif kind == "ties":
+            g = rng.integers(-3, 4, size=d).astype(np.float32)
+        else:
+            g = np.full(d, -2.0, np.float32)
+        gi, gv, ge, _ = run_gpu(g, e, off, ks, k_total=k_total, ws=ws, unaligned=unaligned)
+        assert efs.topk_segmented_status(ws) == 0
+        ri, rv, re = oracle.topk_segmented(g, e, LR, off, ks)
+        o = np.lexsort((gi, np.repeat(np.arange(ks.size), ks)))
+        np.testing.assert_array_equal(gi[o], ri, "t=%d indices" % t)
+        assert_bits_equal(gv[o], rv, "t=%d values" % t)
+        assert_bits_equal(ge, re, "t=%d e'" % t)
+        e = re
