@@ -70,8 +70,7 @@ typedef enum efs_status {
  *   counter  counter object (see above); word 0 receives k_t, the TRUE
  *            count even when it exceeds cap (then the payload is truncated
  *            and must be treated as invalid; e' is complete regardless).
- * Pointers g and e must be 4-byte aligned (16-byte alignment takes the
- * vector path).  NaN entries of p are never kept. */
+ * Pointers g and e must be 4-byte aligned.  NaN entries of p are never kept. */
 efs_status ht_compress(const float *g, float *e, int64_t d, float lr, float lambda,
                        int32_t *idx, float *val, int64_t cap, uint32_t *counter,
                        void *stream);

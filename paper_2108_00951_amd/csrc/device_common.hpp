@@ -53,6 +53,20 @@ __device__ __forceinline__ TileWalk tile_walk(uint32_t ntiles, bool by_xcd) {
     return TileWalk{lo + b / kXcds, hi, n_x};
 }
 
+// A sweep over [0, d) in steps of `step` elements from `first` <= 0 on, so that
+// every step starts on a 128-byte line of e whatever e's alignment (the
+// elements before the first line form a partial first step).
+struct Sweep {
+    int64_t first;
+    uint32_t steps;
+};
+
+inline Sweep sweep_start(const float *e, int64_t d, int64_t step) {
+    const int64_t head = int64_t(((128u - (reinterpret_cast<uintptr_t>(e) & 127u)) & 127u) / 4u);
+    const int64_t first = head == 0 ? 0 : head - step;
+    return Sweep{first, uint32_t((d - first + step - 1) / step)};
+}
+
 // Counter word layout used for single-launch stream compaction: the low 40
 // bits accumulate the number of emitted pairs, the high 24 bits count
 // workgroups that have finished (a ticket, so the last one is known).

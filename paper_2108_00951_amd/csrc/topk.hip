@@ -206,19 +206,6 @@ Workspace carve(void *ws, int64_t d, int64_t k) {
     return w;
 }
 
-// A sweep over [0, d) in steps of `step` elements from `first` <= 0 on, so
-// that every step starts on a 128-byte line of e.
-struct Sweep {
-    int64_t first;
-    uint32_t steps;
-};
-
-Sweep sweep_start(const float *e, int64_t d, int64_t step) {
-    const int64_t head = int64_t(((128u - (reinterpret_cast<uintptr_t>(e) & 127u)) & 127u) / 4u);
-    const int64_t first = head == 0 ? 0 : head - step;
-    return Sweep{first, uint32_t((d - first + step - 1) / step)};
-}
-
 // Inclusive sum of v over the lanes of the wave up to this one.
 __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v) {
     const int lane = threadIdx.x & (kWave - 1);

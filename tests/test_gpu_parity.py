@@ -813,3 +813,36 @@ def test_topk_threshold_bin_sizes(ties, at_zero):
         want = (ri, rv, re)
         assert_payload_equal(st.idx[:k].cpu().numpy(), st.val[:k].cpu().numpy(), ri, rv, "call %d" % t)
         assert_bits_equal(st.e.cpu().numpy(), re, "call %d" % t)
+
+
+@pytest.mark.parametrize("shift_g,shift_e", [(0, 0), (1, 1), (0, 3), (2, 0), (31, 31)])
+@pytest.mark.parametrize("d", [1, 33, 4096, 4127, 8192, 1_000_003])
+def test_ht_views_at_any_alignment(d, shift_g, shift_e):
+    # g and e as views at their own offsets into a buffer: the partial first
+    # tile up to e's first 128-byte line, whole tiles, the partial last one;
+    # nothing written outside e's own elements, telemetry over all of them
+    buf = torch.full((d + 64,), 7.0, dtype=torch.float32, device=DEV)
+    e = buf[shift_e:shift_e + d]
+    e.zero_()
+    idx = torch.empty(d, dtype=torch.int32, device=DEV)
+    val = torch.empty(d, dtype=torch.float32, device=DEV)
+    ctr, tel = efs.new_counter(DEV), efs.new_telemetry(DEV)
+    lam = np.float32(1.5e-4)
+    ref, err2, sent = np.zeros(d, np.float32), 0.0, 0
+    for t in range(3):
+        g_host = synth.small_gradient(4100 + t, d)
+        gbuf = torch.empty(d + 64, dtype=torch.float32, device=DEV)
+        gbuf[shift_g:shift_g + d].copy_(torch.from_numpy(g_host))
+        efs.ht_compress_telemetry(gbuf[shift_g:shift_g + d], e, LR, lam, idx, val, ctr, tel)
+        ri, rv, ref, rk = oracle.ht(g_host, ref, LR, lam)
+        n = efs.counter_value(ctr)
+        assert n == rk
+        assert_payload_equal(idx[:n].cpu().numpy(), val[:n].cpu().numpy(), ri, rv, "d=%d t=%d" % (d, t))
+        assert_bits_equal(e.cpu().numpy(), ref, "d=%d t=%d" % (d, t))
+        err2 += float(np.sum(ref.astype(np.float64) ** 2))
+        sent += rk
+    got = efs.read_telemetry(tel)
+    assert got["sent_total"] == sent and got["calls"] == 3
+    # d sums of binary64 squares in two orders: below d * 2^-52 relative
+    assert abs(got["err2_total"] - err2) <= max(d, 16) * 2.0 ** -52 * err2
+    assert bool((buf[:shift_e] == 7.0).all()) and bool((buf[shift_e + d:] == 7.0).all())
