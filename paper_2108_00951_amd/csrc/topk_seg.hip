@@ -69,10 +69,6 @@ constexpr int kDigit2 = 1 << (kShift1 - kShift2);
 constexpr int kDigit3 = 1 << kShift2;
 constexpr int kIdxBins = 2048;  // index radix for ties: 11 + 10 + 10 bits
 constexpr int kCandLds = 18432;  // candidates the final pass holds in LDS (144 KiB)
-// ... with more than kFinalWideMin segments: a smaller buffer (30 KiB), so
-// that four workgroups share a CU
-constexpr int kCandLdsSmall = 3840;
-constexpr int kFinalWideMin = 256;
 constexpr int64_t kCandPerK = 16;
 constexpr int64_t kCandExtra = 4096;
 
@@ -86,8 +82,8 @@ enum : uint32_t {
 // workgroup: no histogram in memory, bracket or later launch.  Such a segment
 // is one tile wherever it starts.  With only the segments inside one
 // 4096-element block selected so, a step over the 2e4 layers of 2.56e7 elements
-// took 293 us (a fifth of them cut in two by a block boundary), 159 so, and
-// over 161 layers 117.
+// took 293 us (a fifth of them cut in two by a block boundary), 125 so, and
+// over 161 layers 116.
 constexpr int64_t kWgSegMax = 16384;
 
 // log2 of how far the bracket reaches below and above the predicted
@@ -625,12 +621,27 @@ __device__ __forceinline__ void reset_zero(const SegWs &ws, const int64_t *off, 
     f32x4 *fl = reinterpret_cast<f32x4 *>(ws.sweep);
     for (int q = w * kResetBlock + threadIdx.x; q < kSweepGroups / 4; q += nw * kResetBlock)
         fl[q] = z;
-    for (int32_t sg = w; sg < nseg; sg += nw) {
-        if (off[sg + 1] - off[sg] <= kWgSegMax) continue;
-        f32x4 *h1 = reinterpret_cast<f32x4 *>(ws.hist1 + int64_t(sg) * kDigit1);
-        f32x4 *h2 = reinterpret_cast<f32x4 *>(ws.hist2 + int64_t(sg) * kDigit2);
-        for (int q = threadIdx.x; q < kDigit1 / 4; q += kResetBlock) h1[q] = z;
-        for (int q = threadIdx.x; q < kDigit2 / 4; q += kResetBlock) h2[q] = z;
+    // the sizes of up to kResetBlock of its layers w, w + nw, ... at once, then
+    // those with tiles in turn
+    __shared__ int32_t s_list[kResetBlock];
+    __shared__ uint32_t s_n;
+    const int32_t per = (nseg - w + nw - 1) / nw;
+    for (int32_t g0 = 0; g0 < per; g0 += kResetBlock) {
+        if (threadIdx.x == 0) s_n = 0u;
+        __syncthreads();
+        const int32_t i = g0 + int32_t(threadIdx.x);
+        if (i < per) {
+            const int32_t sg = w + i * nw;
+            if (off[sg + 1] - off[sg] > kWgSegMax) s_list[atomicAdd(&s_n, 1u)] = sg;
+        }
+        __syncthreads();
+        for (uint32_t j = 0; j < s_n; ++j) {
+            f32x4 *h1 = reinterpret_cast<f32x4 *>(ws.hist1 + int64_t(s_list[j]) * kDigit1);
+            f32x4 *h2 = reinterpret_cast<f32x4 *>(ws.hist2 + int64_t(s_list[j]) * kDigit2);
+            for (int q = threadIdx.x; q < kDigit1 / 4; q += kResetBlock) h1[q] = z;
+            for (int q = threadIdx.x; q < kDigit2 / 4; q += kResetBlock) h2[q] = z;
+        }
+        __syncthreads();   // the list is rewritten
     }
 }
 
@@ -1666,7 +1677,7 @@ __device__ void select1_segment(const SegWs &ws, int32_t s, uint32_t *s_wave, ui
 // segments each and select those without tiles, which pass1 left alone: a
 // wave each where a wave can, the rest by the workgroup one after another.
 // Both kinds in one launch: the first keep few CUs busy for a few round trips.
-__global__ __launch_bounds__(kBlock) void seg_select_kernel(const float *__restrict__ g, float *e,
+__global__ __launch_bounds__(kBlock, 5) void seg_select_kernel(const float *__restrict__ g, float *e,
                                                             float lr, int32_t *__restrict__ idx,
                                                             float *__restrict__ val, SegWs ws,
                                                             int32_t nseg, int32_t nbig,
@@ -1694,15 +1705,33 @@ __global__ __launch_bounds__(kBlock) void seg_select_kernel(const float *__restr
     }
     const int32_t s0 = (int32_t(blockIdx.x) - nbig) * group;
     const int32_t wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave);
-    if (wave < group && s0 + wave < nseg) {
-        const SegInfo inf = ws.info[s0 + wave];
+    // the group's tables and hints, a dword a lane (one round trip): lanes
+    // 16 i .. 16 i + 15 hold segment s0 + i's SegInfo, 8 i .. 8 i + 7 its hint
+    constexpr int kInfoWords = sizeof(SegInfo) / 4, kHintWords = sizeof(SegHint) / 4;
+    static_assert(kWaves * kInfoWords == kWave, "one wave holds a group's tables");
+    const int lane = threadIdx.x & (kWave - 1);
+    const int32_t have = min(group, nseg - s0);
+    uint32_t tab = 0u, hints = 0u;
+    if (lane / kInfoWords < have)
+        tab = reinterpret_cast<const uint32_t *>(ws.info + s0 + lane / kInfoWords)[lane % kInfoWords];
+    if (lane / kHintWords < have)
+        hints = reinterpret_cast<const uint32_t *>(ws.hint + s0 + lane / kHintWords)[lane % kHintWords];
+    if (wave < have) {
+        const SegInfo inf = tab_info(tab, kInfoWords * wave);
         if (inf.size > 0 && wave_layer(inf.size, inf.k)) select_in_wave(g, e, lr, idx, val, inf);
     }
     for (int b = threadIdx.x; b < 2048; b += kBlock) hist[b] = 0u;
-    for (int32_t s = s0; s < min(s0 + group, nseg); ++s) {
-        const SegInfo inf = ws.info[s];
+#pragma unroll 1
+    for (int32_t i = 0; i < have; ++i) {
+        const int32_t s = s0 + i;
+        const SegInfo inf = tab_info(tab, kInfoWords * i);
         if (inf.size > kWgSegMax || wave_layer(inf.size, inf.k)) continue;
-        const SegHint oh = ws.hint[s];
+        SegHint oh = {};
+        oh.key = tab_word(hints, kHintWords * i);
+        oh.prev = tab_word(hints, kHintWords * i + 1);
+        oh.prev2 = tab_word(hints, kHintWords * i + 2);
+        oh.magic = tab_word(hints, kHintWords * i + 3);
+        oh.width = tab_word(hints, kHintWords * i + 4);
         const bool hinted = hint_usable(oh);
         Bracket br = {0u, 0u};
         if (hinted) br = bracket_of(oh);
@@ -1719,7 +1748,7 @@ __global__ __launch_bounds__(kBlock) void seg_select_kernel(const float *__restr
             if (hinted && !inside) {
                 wl = min(wl + 1u, kWidthMax);
                 wh = min(wh + 1u, kWidthMax);
-            } else if (hinted && int64_t(listed) > 2 * inf.k + 64 && wl > kWidthMin) {
+            } else if (hinted && int64_t(listed) > 2 * inf.k + 24 && wl > kWidthMin) {
                 --wl;
             }
             ws.hint[s] = next_hint(oh, T, make_widths(wl, wh));
@@ -1930,11 +1959,9 @@ __global__ __launch_bounds__(kBlock) void seg_pass2_kernel(float *__restrict__ e
 // final: each segment's exact threshold, its ties, the last pairs
 // ---------------------------------------------------------------------------
 
-template <int kCap>
 struct FinalShared {
-    static constexpr int cap = kCap;
     uint32_t hist[kIdxBins];
-    uint2 cand[kCap];
+    uint2 cand[kCandLds];
     uint32_t wave[kWaves];
     uint32_t out[3];
     uint32_t cursor;
@@ -1946,8 +1973,8 @@ constexpr int kUnroll = 8;               // items loaded per thread at a time
 // Calls f(key, index, bits of p) for every item of the segment's selection
 // set: the candidate list (LDS or global), or, in scan mode, every element
 // of the segment.  kUnroll loads per thread are in flight together.
-template <int kMode, bool kLds, typename Sh, typename F>
-__device__ __forceinline__ void for_items(const Sh &sh, const uint2 *cand,
+template <int kMode, bool kLds, typename F>
+__device__ __forceinline__ void for_items(const FinalShared &sh, const uint2 *cand,
                                           const float *e, const SegInfo &inf, int64_t n, F f) {
     for (int64_t base = 0; base < n; base += int64_t(kUnroll) * kBlock) {
         uint2 it[kUnroll];
@@ -1975,8 +2002,8 @@ __device__ __forceinline__ void for_items(const Sh &sh, const uint2 *cand,
 // index: bits 30..20, 19..10, 9..0, unless all are kept), emit every item
 // above T and the chosen ties from payload slot `cursor0` on, clear their e,
 // and record T as the next call's hint.
-template <int kMode, bool kLds, typename Sh>
-__device__ void finish(Sh &sh, const SegInfo &inf, const uint2 *cand, int64_t n,
+template <int kMode, bool kLds>
+__device__ void finish(FinalShared &sh, const SegInfo &inf, const uint2 *cand, int64_t n,
                        float *e, int32_t *idx, float *val, uint32_t T, uint32_t need3,
                        uint32_t ties, uint32_t cursor0, SegHint *hint, uint32_t width) {
     const int tid = threadIdx.x;
@@ -2022,8 +2049,8 @@ __device__ void finish(Sh &sh, const SegInfo &inf, const uint2 *cand, int64_t n,
 // Radix path: D1 from pass1, digit 2 from pass2's histogram of the keys in
 // D1, digit 3 from a pass over the items.  Scan mode also emits every key
 // above D1 (pass2 left them in place).
-template <int kMode, bool kLds, typename Sh>
-__device__ void final_select(Sh &sh, const SegInfo &inf, const SegState &st,
+template <int kMode, bool kLds>
+__device__ void final_select(FinalShared &sh, const SegInfo &inf, const SegState &st,
                              const uint2 *cand, int64_t n, float *e, int32_t *idx, float *val,
                              const uint32_t *hist2, SegHint *hint, uint32_t width) {
     const int tid = threadIdx.x;
@@ -2055,8 +2082,8 @@ __device__ void final_select(Sh &sh, const SegInfo &inf, const SegState &st,
 // da and listed the `ca` candidates of bin da; rank those by the low
 // `shift` bits of key - lo (the exact threshold T), then by index among
 // keys equal to T, and emit the `needa` kept ones into the last slots.
-template <bool kLds, typename Sh>
-__device__ void final_fast(Sh &sh, const SegInfo &inf, const SegState &st,
+template <bool kLds>
+__device__ void final_fast(FinalShared &sh, const SegInfo &inf, const SegState &st,
                            const uint2 *list, int64_t n, float *e, int32_t *idx, float *val,
                            SegHint *hint, uint32_t width) {
     const int tid = threadIdx.x;
@@ -2145,9 +2172,8 @@ __device__ __forceinline__ void final_fast_wave(float *__restrict__ e, int32_t *
     if (lane == 0u) *hint = next_hint(oh, T, width);
 }
 
-template <typename Sh>
 __device__ void final_segment(float *__restrict__ e, int32_t *__restrict__ idx,
-                              float *__restrict__ val, const SegWs &ws, int32_t s, Sh &sh) {
+                              float *__restrict__ val, const SegWs &ws, int32_t s, FinalShared &sh) {
     const SegState st = ws.st[s];
     if (st.mode != kModeCand && st.mode != kModeScan && st.mode != kModeFast) return;
     const SegInfo inf = ws.info[s];
@@ -2163,7 +2189,7 @@ __device__ void final_segment(float *__restrict__ e, int32_t *__restrict__ idx,
     const int64_t n = fast ? int64_t(st.needa ? min(st.ca, st.tcur) : 0u)
                            : min(int64_t(st.ccur), inf.ccap);
     const uint2 *cand = ws.cand + inf.coff + (fast ? st.ccur : 0u);
-    const bool lds = n <= Sh::cap;
+    const bool lds = n <= kCandLds;
     if (lds) {
         for (int64_t base = 0; base < n; base += int64_t(kUnroll) * kBlock) {
             uint2 v[kUnroll];
@@ -2189,19 +2215,19 @@ __device__ void final_segment(float *__restrict__ e, int32_t *__restrict__ idx,
     }
 }
 
-// One workgroup per CU at most with the large candidate buffer, four with
-// the small one (a larger list is ranked from global memory), looping over
-// the segments b, b + grid, ...  Most need nothing here (one tile, none,
+// One workgroup per CU at most, looping over the segments b, b + grid, ...
+// (each adds its count to one word at the end, 13 ns apiece: with four a CU a
+// call over 2e4 layers, none of which needs this launch, spent 15 us in it).
+// Most need nothing here (one tile, none,
 // all), so the workgroup first reads the modes of up to kBlock of its
 // segments at once and then runs only those with something to rank (one
 // dependent read per segment in turn was the larger cost with thousands of
 // segments).
-template <int kCap>
 __global__ __launch_bounds__(kBlock) void seg_final_kernel(float *__restrict__ e,
                                                            int32_t *__restrict__ idx,
                                                            float *__restrict__ val, SegWs ws,
                                                            int32_t nseg) {
-    __shared__ FinalShared<kCap> sh;
+    __shared__ FinalShared sh;
     __shared__ int32_t s_list[kBlock];
     __shared__ uint32_t s_wave[kWaves];
     if (ws.ctl->status != 0u) return;
@@ -2272,7 +2298,9 @@ hipError_t launch_topk_segmented(const float *g, float *e, int64_t d, float lr, 
     const int64_t max_tiles = (d + kTile - 1) / kTile + nseg;
     while (((max_tiles - 1) >> ws.sweep_shift) >= kSweepGroups) ++ws.sweep_shift;
 
-    const uint32_t zero_grid = persistent_grid(nseg);  // one segment's histograms per pass
+    // one segment's histograms a workgroup, four workgroups a CU at most
+    const int64_t cus = device_cu_count();
+    const uint32_t zero_grid = uint32_t(min(int64_t(nseg), 4 * cus));
     if (nseg <= kResetSingleMax) {
         seg_reset_kernel<<<1 + zero_grid, kResetBlock, 0, stream>>>(ws, offsets, k, nseg, d, k_total);
     } else {
@@ -2295,7 +2323,6 @@ hipError_t launch_topk_segmented(const float *g, float *e, int64_t d, float lr, 
         seg_pass1_kernel<true><<<grid, kBlock, 0, stream>>>(g, e, lr, idx, val, nseg, ws, uint32_t(slice));
     else
         seg_pass1_kernel<false><<<grid, kBlock, 0, stream>>>(g, e, lr, idx, val, nseg, ws, uint32_t(slice));
-    const int64_t cus = device_cu_count();
     // one segment a workgroup while that fills the chip at most twice over,
     // then four
     const int32_t nbig = int32_t(min(int64_t(nseg), 4 * cus));
@@ -2306,12 +2333,7 @@ hipError_t launch_topk_segmented(const float *g, float *e, int64_t d, float lr, 
         seg_pass2_kernel<true><<<grid, kBlock, 0, stream>>>(e, idx, val, nseg, ws, uint32_t(slice));
     else
         seg_pass2_kernel<false><<<grid, kBlock, 0, stream>>>(e, idx, val, nseg, ws, uint32_t(slice));
-    if (nseg > kFinalWideMin)
-        seg_final_kernel<kCandLdsSmall><<<uint32_t(min(int64_t(nseg), 4 * cus)), kBlock, 0, stream>>>(
-            e, idx, val, ws, nseg);
-    else
-        seg_final_kernel<kCandLds><<<uint32_t(min(int64_t(nseg), cus)), kBlock, 0, stream>>>(
-            e, idx, val, ws, nseg);
+    seg_final_kernel<<<uint32_t(min(int64_t(nseg), cus)), kBlock, 0, stream>>>(e, idx, val, ws, nseg);
     return hipGetLastError();
 }
 
