@@ -380,6 +380,7 @@ def prepare_sparse_apply(payloads: Sequence[Tuple], d: int, mode: int, x, worksp
 
     def call():
         _check(lib, fn(*args))
+    call.tensors = (tuple(payloads), x, m, workspace)   # alive as long as the pointers in args
     return call
 
 
@@ -406,6 +407,7 @@ def prepare_sparse_accumulate(payloads: Sequence[Tuple], d: int, out, workspace,
 
     def call():
         _check(lib, fn(*args))
+    call.tensors = (tuple(payloads), out, workspace)   # alive as long as the pointers in args
     return call
 
 
