@@ -4,7 +4,7 @@
 // of them: the largest keys (31-bit patterns of |p|), equal keys to the
 // lower index, exactly as the flat Top-k ranks them.
 //
-// Segments of more than kWgSegMax elements are cut into tiles, the 4096-element
+// Segments of more than 16,384 elements (4,096 among few) are cut into tiles, the 4096-element
 // blocks of the vector clipped to the segment, so every whole tile is 16-byte
 // aligned.  The two sweeps take short slices of consecutive tiles in turn
 // across the vector (longer ones with many segments).  Shorter segments have
@@ -78,13 +78,16 @@ enum : uint32_t {
     kModeHit = 6    // the same, from its bracket
 };
 
-// Segments of at most kWgSegMax elements are selected in pass 1 by one
-// workgroup: no histogram in memory, bracket or later launch.  Such a segment
-// is one tile wherever it starts.  With only the segments inside one
-// 4096-element block selected so, a step over the 2e4 layers of 2.56e7 elements
-// took 293 us (a fifth of them cut in two by a block boundary), 125 so, and
-// over 161 layers 116.
-constexpr int64_t kWgSegMax = 16384;
+// Segments of at most SegWs::wg_max elements are selected by one workgroup: no
+// histogram in memory, bracket counts or later launch.  Such a segment has no
+// tiles, wherever it starts: when only the segments inside one 4096-element
+// block were selected so, a fifth of 2e4 layers, cut in two by a block
+// boundary, took the path of the large ones (2.56e7 elements: 276 us a step,
+// 125 so).  Up to kSegManyMin segments, which leave most of the chip idle,
+// the limit is one 4096-element read: a longer segment's reads in turn would
+// hold up the launch (161 layers over 2.56e7 elements: 19 us, 9 so).
+constexpr int64_t kWgSegMax = 16384, kWgSegFew = 4096;
+constexpr int32_t kSegManyMin = 1024;
 
 // log2 of how far the bracket reaches below and above the predicted
 // threshold, each adapted per segment between these (2^19 keys are 3-6 % of
@@ -101,8 +104,9 @@ constexpr uint32_t kChunk = kWorkPerLane * kWave;
 // The sweeps take slices of `slice` consecutive tiles (at most
 // kSliceTilesMax), slice b + i * grid for workgroup b: the resident
 // workgroups stream one compact window of the vector at a time (measured
-// faster than one long range per workgroup), and a slice is long enough to
-// amortise its flushes.
+// faster than one long range per workgroup: one slice of seven tiles for each
+// resident workgroup, 79 us a pass 1 at 2.56e7 elements, 72 so), and a slice is
+// long enough to amortise its flushes.
 constexpr int64_t kSliceTilesMax = 4;
 // With more segments than a two-round search covers, a slice starts with a
 // third round of dependent reads: the slices are then made as long as the
@@ -244,6 +248,7 @@ struct SegWs {
     int64_t ccap_total;
     uint32_t work_cap;
     uint32_t sweep_shift;   // tile t is in group t >> sweep_shift
+    int64_t wg_max;         // longest segment without tiles
 };
 
 struct SegLayout {
@@ -462,10 +467,11 @@ __device__ __forceinline__ bool slice_meets(int j, uint32_t lo, uint32_t hi) {
     return uint32_t(j) * (4u * kBlock) < hi && uint32_t(j + 1) * (4u * kBlock) > lo;
 }
 
-// Tiles of a segment: none when it is selected whole (at most kWgSegMax
-// elements), else the 4096-element blocks it overlaps (at least five).
-__host__ __device__ __forceinline__ int64_t segment_tiles(int64_t off, int64_t size) {
-    return size <= kWgSegMax ? 0 : ((off + size - 1) / kTile) - (off / kTile) + 1;
+// Tiles of a segment: none when it is selected whole (at most wg_max
+// elements), else the 4096-element blocks it overlaps.
+__host__ __device__ __forceinline__ int64_t segment_tiles(int64_t off, int64_t size,
+                                                          int64_t wg_max) {
+    return size <= wg_max ? 0 : ((off + size - 1) / kTile) - (off / kTile) + 1;
 }
 
 // Tile t of segment `inf`: the block start and the element
@@ -550,14 +556,14 @@ __device__ __forceinline__ SegIn load_seg(const int64_t *off, const int64_t *kin
 // slots, tiles and work-list slots; `bad` is set for a layer outside the
 // rules (negative size or k, outside [0, d)).
 __device__ __forceinline__ Sums seg_sums(const SegIn &in, int32_t s, int32_t nseg, int64_t d,
-                                         bool &bad) {
+                                         int64_t wg_max, bool &bad) {
     Sums v = {0, 0, 0u, 0u};
     if (s >= nseg) return v;
     const int64_t size = in.hi - in.lo;
     if (size < 0 || in.k < 0 || in.lo < 0 || in.hi > d) bad = true;
     if (size >= 0 && in.k >= 0) {
         const int64_t keff = in.k < size ? in.k : size;
-        const uint32_t nt = uint32_t(segment_tiles(in.lo, size));
+        const uint32_t nt = uint32_t(segment_tiles(in.lo, size, wg_max));
         const int64_t ccap = (nt > 0u && keff > 0 && keff < size) ? kCandPerK * keff + kCandExtra : 0;
         // bracket path: the pairs above the bracket (at most k) and the
         // candidates (at most ccap), kChunk per work item
@@ -576,7 +582,7 @@ __device__ __forceinline__ Sums reset_chunk(const SegWs &ws, const SegIn &in, in
                                             bool &bad) {
     SegHint h = {};
     if (s < nseg) h = ws.hint[s];  // used after the scan
-    const Sums v = seg_sums(in, s, nseg, d, bad);
+    const Sums v = seg_sums(in, s, nseg, d, ws.wg_max, bad);
     Sums tot;
     const Sums ex = reset_scan(v, s_wave, tot);
     if (s < nseg) {
@@ -632,7 +638,7 @@ __device__ __forceinline__ void reset_zero(const SegWs &ws, const int64_t *off, 
         const int32_t i = g0 + int32_t(threadIdx.x);
         if (i < per) {
             const int32_t sg = w + i * nw;
-            if (off[sg + 1] - off[sg] > kWgSegMax) s_list[atomicAdd(&s_n, 1u)] = sg;
+            if (off[sg + 1] - off[sg] > ws.wg_max) s_list[atomicAdd(&s_n, 1u)] = sg;
         }
         __syncthreads();
         for (uint32_t j = 0; j < s_n; ++j) {
@@ -726,7 +732,7 @@ __global__ __launch_bounds__(kResetBlock) void seg_reset_sums_kernel(SegWs ws,
     __syncthreads();
     const int32_t s = int32_t(blockIdx.x) * kResetBlock + int32_t(threadIdx.x);
     bool bad = false;
-    const Sums v = seg_sums(load_seg(off, kin, s, nseg), s, nseg, d, bad);
+    const Sums v = seg_sums(load_seg(off, kin, s, nseg), s, nseg, d, ws.wg_max, bad);
     if (bad) atomicOr(&s_bad, 1u);
     Sums tot;
     reset_scan(v, s_wave, tot);   // its barriers also order s_bad
@@ -1725,7 +1731,7 @@ __global__ __launch_bounds__(kBlock, 5) void seg_select_kernel(const float *__re
     for (int32_t i = 0; i < have; ++i) {
         const int32_t s = s0 + i;
         const SegInfo inf = tab_info(tab, kInfoWords * i);
-        if (inf.size > kWgSegMax || wave_layer(inf.size, inf.k)) continue;
+        if (inf.size > ws.wg_max || wave_layer(inf.size, inf.k)) continue;
         SegHint oh = {};
         oh.key = tab_word(hints, kHintWords * i);
         oh.prev = tab_word(hints, kHintWords * i + 1);
@@ -2293,6 +2299,7 @@ hipError_t launch_topk_segmented(const float *g, float *e, int64_t d, float lr, 
     ws.sweep = reinterpret_cast<uint32_t *>(base + L.sweep);
     ws.ccap_total = L.ccap_total;
     ws.work_cap = uint32_t(L.work_cap);
+    ws.wg_max = nseg > kSegManyMin ? kWgSegMax : kWgSegFew;
     // every tile index is below ceil(d / kTile) + nseg, so its group is below
     // kSweepGroups
     const int64_t max_tiles = (d + kTile - 1) / kTile + nseg;
@@ -2314,7 +2321,7 @@ hipError_t launch_topk_segmented(const float *g, float *e, int64_t d, float lr, 
     // slices: the tiles spread over kSliceWorkgroupsPerCU workgroups per CU
     // (4 resident), at most kSliceTilesMax tiles each (kSliceTilesMaxMany
     // with many segments)
-    const int64_t wgs = int64_t(device_cu_count()) * kSliceWorkgroupsPerCU;
+    const int64_t wgs = cus * kSliceWorkgroupsPerCU;
     const int64_t slice_max = nseg > kSearchTwoRounds ? kSliceTilesMaxMany : kSliceTilesMax;
     const int64_t slice = max(int64_t(1), min(slice_max, (max_tiles + wgs - 1) / wgs));
     const uint32_t grid = uint32_t(min(wgs, (max_tiles + slice - 1) / slice));
