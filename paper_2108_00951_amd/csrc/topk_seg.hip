@@ -4,9 +4,11 @@
 // of them: the largest keys (31-bit patterns of |p|), equal keys to the
 // lower index, exactly as the flat Top-k ranks them.
 //
-// Segments of more than 16,384 elements (4,096 among few) are cut into tiles, the 4096-element
-// blocks of the vector clipped to the segment, so every whole tile is 16-byte
-// aligned.  The two sweeps take short slices of consecutive tiles in turn
+// Segments of more than 16,384 elements (4,096 among few) are cut into tiles,
+// the 4096-element blocks of the vector clipped to the segment.  Blocks start
+// on 128-byte lines of e, whatever e's and g's own alignment (the first block
+// is the shorter one); g is read in 16-byte accesses at 4-byte alignment.
+// The two sweeps take short slices of consecutive tiles in turn
 // across the vector (longer ones with many segments).  Shorter segments have
 // no tiles: a workgroup or a wave selects each whole.  Five launches (six
 // above 2048 segments, where the reset takes two):
@@ -249,6 +251,7 @@ struct SegWs {
     uint32_t work_cap;
     uint32_t sweep_shift;   // tile t is in group t >> sweep_shift
     int64_t wg_max;         // longest segment without tiles
+    int64_t phase;          // elements of e's first 128-byte line before e
 };
 
 struct SegLayout {
@@ -461,31 +464,106 @@ __device__ __forceinline__ uint32_t tile_off(int j, int c) {
     return uint32_t(j * kBlock + int(threadIdx.x)) * 4u + uint32_t(c);
 }
 
-// Slice j of every thread's elements covers offsets [j * 1024, (j + 1) * 1024)
-// of the block: whether it meets [lo, hi) (the same for the whole workgroup).
-__device__ __forceinline__ bool slice_meets(int j, uint32_t lo, uint32_t hi) {
-    return uint32_t(j) * (4u * kBlock) < hi && uint32_t(j + 1) * (4u * kBlock) > lo;
-}
-
 // Tiles of a segment: none when it is selected whole (at most wg_max
-// elements), else the 4096-element blocks it overlaps.
+// elements), else the 4096-element blocks it overlaps.  Element i is in block
+// (i + phase) / kTile, phase being e's offset in its 128-byte line.
 __host__ __device__ __forceinline__ int64_t segment_tiles(int64_t off, int64_t size,
-                                                          int64_t wg_max) {
-    return size <= wg_max ? 0 : ((off + size - 1) / kTile) - (off / kTile) + 1;
+                                                          int64_t wg_max, int64_t phase) {
+    return size <= wg_max ? 0
+                          : (off + phase + size - 1) / kTile - (off + phase) / kTile + 1;
 }
 
-// Tile t of segment `inf`: the block start and the element
-// range [lo, hi).
+// Tile t of segment `inf`: the block start (below 0 for the first block of a
+// vector off a line) and the element range [lo, hi).
 struct TileRange {
     int64_t block0, lo, hi;
 };
 
-__device__ __forceinline__ TileRange tile_range(const SegInfo &inf, uint32_t t) {
+__device__ __forceinline__ TileRange tile_range(const SegInfo &inf, uint32_t t, int64_t phase) {
     TileRange r;
-    r.block0 = (inf.off / kTile + int64_t(t - inf.tile0)) * kTile;
+    r.block0 = ((inf.off + phase) / kTile + int64_t(t - inf.tile0)) * kTile - phase;
     r.lo = max(inf.off, r.block0);
     r.hi = min(inf.off + inf.size, r.block0 + kTile);
     return r;
+}
+
+// p = e + lr*g (kStep, written into e) or e of this thread's elements of a
+// tile; `valid` marks those inside it.  All reads go out before the first is
+// used.  In a clipped tile a thread's four neighbours are read and written as
+// one vector where all are inside, so the two ends of a segment cost hardly
+// more than a whole tile.  Against element-wise accesses in clipped tiles and
+// off 16-byte boundaries, a step with its update: 1.65e7 elements in 1,521
+// segments, three elements off, 159 -> 110 us; aligned, 3.3e7 in 297 124.5 ->
+// 120.7, 2.56e7 in 161 108.4 -> 105.4.
+template <bool kStep>
+__device__ __forceinline__ void tile_load(const float *__restrict__ g, float *e, float lr,
+                                          const TileRange &r, float (&p)[kVecPerThread][4],
+                                          uint32_t &valid) {
+    const f32x4u *g4 = reinterpret_cast<const f32x4u *>(g + r.block0) + threadIdx.x;
+    f32x4 *e4 = reinterpret_cast<f32x4 *>(e + r.block0) + threadIdx.x;
+    f32x4 gv[kVecPerThread], ev[kVecPerThread];
+    if (r.lo == r.block0 && r.hi == r.block0 + kTile) {
+#pragma unroll
+        for (int j = 0; j < kVecPerThread; ++j) {
+            if (kStep) gv[j] = __builtin_nontemporal_load(g4 + j * kBlock);
+            ev[j] = kStep ? __builtin_nontemporal_load(e4 + j * kBlock) : e4[j * kBlock];
+        }
+#pragma unroll
+        for (int j = 0; j < kVecPerThread; ++j) {
+            f32x4 v;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                v[c] = kStep ? ef_accumulate(ev[j][c], lr, gv[j][c]) : ev[j][c];
+                p[j][c] = v[c];
+            }
+            if (kStep) __builtin_nontemporal_store(v, e4 + j * kBlock);
+        }
+        valid = 0xffffu;
+        return;
+    }
+    const uint32_t lo = uint32_t(r.lo - r.block0), hi = uint32_t(r.hi - r.block0);
+    const float *gb = g + r.block0;
+    float *eb = e + r.block0;
+    valid = 0u;
+#pragma unroll
+    for (int j = 0; j < kVecPerThread; ++j) {
+        const f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
+        gv[j] = z;
+        ev[j] = z;
+        const uint32_t o = tile_off(j, 0);
+        if (o >= lo && o + 4u <= hi) {
+            if (kStep) gv[j] = __builtin_nontemporal_load(g4 + j * kBlock);
+            ev[j] = kStep ? __builtin_nontemporal_load(e4 + j * kBlock) : e4[j * kBlock];
+            valid |= 0xfu << (4 * j);
+        } else if (o + 4u > lo && o < hi) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (o + uint32_t(c) >= lo && o + uint32_t(c) < hi) {
+                    if (kStep) gv[j][c] = gb[o + c];
+                    ev[j][c] = eb[o + c];
+                    valid |= 1u << (4 * j + c);
+                }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < kVecPerThread; ++j) {
+        const uint32_t here = (valid >> (4 * j)) & 0xfu;
+        f32x4 v;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            v[c] = kStep ? ef_accumulate(ev[j][c], lr, gv[j][c]) : ev[j][c];
+            p[j][c] = v[c];
+        }
+        if (!kStep) continue;
+        if (here == 0xfu) {
+            __builtin_nontemporal_store(v, e4 + j * kBlock);
+        } else if (here != 0u) {
+            const uint32_t o = tile_off(j, 0);
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if ((here >> c) & 1u) eb[o + c] = v[c];
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -556,14 +634,14 @@ __device__ __forceinline__ SegIn load_seg(const int64_t *off, const int64_t *kin
 // slots, tiles and work-list slots; `bad` is set for a layer outside the
 // rules (negative size or k, outside [0, d)).
 __device__ __forceinline__ Sums seg_sums(const SegIn &in, int32_t s, int32_t nseg, int64_t d,
-                                         int64_t wg_max, bool &bad) {
+                                         int64_t wg_max, int64_t phase, bool &bad) {
     Sums v = {0, 0, 0u, 0u};
     if (s >= nseg) return v;
     const int64_t size = in.hi - in.lo;
     if (size < 0 || in.k < 0 || in.lo < 0 || in.hi > d) bad = true;
     if (size >= 0 && in.k >= 0) {
         const int64_t keff = in.k < size ? in.k : size;
-        const uint32_t nt = uint32_t(segment_tiles(in.lo, size, wg_max));
+        const uint32_t nt = uint32_t(segment_tiles(in.lo, size, wg_max, phase));
         const int64_t ccap = (nt > 0u && keff > 0 && keff < size) ? kCandPerK * keff + kCandExtra : 0;
         // bracket path: the pairs above the bracket (at most k) and the
         // candidates (at most ccap), kChunk per work item
@@ -582,7 +660,7 @@ __device__ __forceinline__ Sums reset_chunk(const SegWs &ws, const SegIn &in, in
                                             bool &bad) {
     SegHint h = {};
     if (s < nseg) h = ws.hint[s];  // used after the scan
-    const Sums v = seg_sums(in, s, nseg, d, ws.wg_max, bad);
+    const Sums v = seg_sums(in, s, nseg, d, ws.wg_max, ws.phase, bad);
     Sums tot;
     const Sums ex = reset_scan(v, s_wave, tot);
     if (s < nseg) {
@@ -732,7 +810,7 @@ __global__ __launch_bounds__(kResetBlock) void seg_reset_sums_kernel(SegWs ws,
     __syncthreads();
     const int32_t s = int32_t(blockIdx.x) * kResetBlock + int32_t(threadIdx.x);
     bool bad = false;
-    const Sums v = seg_sums(load_seg(off, kin, s, nseg), s, nseg, d, ws.wg_max, bad);
+    const Sums v = seg_sums(load_seg(off, kin, s, nseg), s, nseg, d, ws.wg_max, ws.phase, bad);
     if (bad) atomicOr(&s_bad, 1u);
     Sums tot;
     reset_scan(v, s_wave, tot);   // its barriers also order s_bad
@@ -1436,7 +1514,6 @@ __device__ __forceinline__ void select_in_wave(const float *__restrict__ g, floa
 
 // Tiles [t0, t1) of pass1; every selection, count and histogram is flushed
 // before it returns (the LDS histogram is left zero).
-template <bool kAligned>
 __device__ void pass1_slice(const float *__restrict__ g, float *__restrict__ e, float lr,
                             int32_t *__restrict__ idx, float *__restrict__ val, int32_t nseg,
                             const SegWs &ws, uint32_t t0, uint32_t t1, uint32_t *hist, Stage &sg) {
@@ -1479,52 +1556,10 @@ __device__ void pass1_slice(const float *__restrict__ g, float *__restrict__ e, 
             st = ws.st + s;
             tab = load_seg_table(ws, nseg, s + 1);
         }
-        const TileRange r = tile_range(inf, t);
+        const TileRange r = tile_range(inf, t, ws.phase);
         float p[kVecPerThread][4];
-        uint32_t valid = 0;
-        if (kAligned && r.lo == r.block0 && r.hi == r.block0 + kTile) {
-            const f32x4 *g4 = reinterpret_cast<const f32x4 *>(g + r.block0);
-            f32x4 *e4 = reinterpret_cast<f32x4 *>(e + r.block0);
-            f32x4 gv[kVecPerThread], ev[kVecPerThread];
-#pragma unroll
-            for (int j = 0; j < kVecPerThread; ++j) {
-                gv[j] = __builtin_nontemporal_load(g4 + j * kBlock + threadIdx.x);
-                ev[j] = __builtin_nontemporal_load(e4 + j * kBlock + threadIdx.x);
-            }
-#pragma unroll
-            for (int j = 0; j < kVecPerThread; ++j) {
-                f32x4 pv;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    pv[c] = ef_accumulate(ev[j][c], lr, gv[j][c]);
-                    p[j][c] = pv[c];
-                }
-                __builtin_nontemporal_store(pv, e4 + j * kBlock + threadIdx.x);
-            }
-            valid = 0xffffu;
-        } else {
-            // a segment's first or last block: only its own elements are
-            // read and written (the rest of the block belongs to
-            // neighbours); slices outside them are skipped
-            const uint32_t lo = uint32_t(r.lo - r.block0), hi = uint32_t(r.hi - r.block0);
-            const float *gb = g + r.block0;
-            float *eb = e + r.block0;
-#pragma unroll
-            for (int j = 0; j < kVecPerThread; ++j) {
-#pragma unroll
-                for (int c = 0; c < 4; ++c) p[j][c] = 0.0f;
-                if (!slice_meets(j, lo, hi)) continue;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const uint32_t o = tile_off(j, c);
-                    if (o >= lo && o < hi) {
-                        p[j][c] = ef_accumulate(eb[o], lr, gb[o]);
-                        eb[o] = p[j][c];
-                        valid |= 1u << (4 * j + c);
-                    }
-                }
-            }
-        }
+        uint32_t valid;
+        tile_load<true>(g, e, lr, r, p, valid);
         uint32_t emit_mask = 0, cand_mask = 0;
 #pragma unroll
         for (int j = 0; j < kVecPerThread; ++j) {
@@ -1553,7 +1588,6 @@ __device__ void pass1_slice(const float *__restrict__ g, float *__restrict__ e, 
     __syncthreads();  // the next slice starts with another segment's state
 }
 
-template <bool kAligned>
 __global__ __launch_bounds__(kBlock, 4) void seg_pass1_kernel(const float *__restrict__ g,
                                                            float *__restrict__ e, float lr,
                                                            int32_t *__restrict__ idx,
@@ -1565,7 +1599,7 @@ __global__ __launch_bounds__(kBlock, 4) void seg_pass1_kernel(const float *__res
     const uint32_t T = ws.ctl->tiles;
     for (int b = threadIdx.x; b < kDigit1; b += kBlock) hist[b] = 0u;
     for (uint32_t t0 = blockIdx.x * slice; t0 < T; t0 += gridDim.x * slice)
-        pass1_slice<kAligned>(g, e, lr, idx, val, nseg, ws, t0, min(T, t0 + slice), hist, sg);
+        pass1_slice(g, e, lr, idx, val, nseg, ws, t0, min(T, t0 + slice), hist, sg);
 }
 
 // ---------------------------------------------------------------------------
@@ -1769,7 +1803,6 @@ __global__ __launch_bounds__(kBlock, 5) void seg_select_kernel(const float *__re
 // ---------------------------------------------------------------------------
 
 // The radix path's sweep over tiles [t0, t1).
-template <bool kAligned>
 __device__ void pass2_tiles(float *__restrict__ e, int32_t *__restrict__ idx,
                             float *__restrict__ val, int32_t nseg, const SegWs &ws, uint32_t t0,
                             uint32_t t1, uint32_t *hist, Stage &sg) {
@@ -1799,36 +1832,10 @@ __device__ void pass2_tiles(float *__restrict__ e, int32_t *__restrict__ idx,
             t = next - 1;  // nothing to do in this segment: skip its tiles
             continue;
         }
-        const TileRange r = tile_range(inf, t);
+        const TileRange r = tile_range(inf, t, ws.phase);
         float p[kVecPerThread][4];
-        uint32_t valid = 0;
-        if (kAligned && r.lo == r.block0 && r.hi == r.block0 + kTile) {
-            const f32x4 *e4 = reinterpret_cast<const f32x4 *>(e + r.block0);
-#pragma unroll
-            for (int j = 0; j < kVecPerThread; ++j) {
-                const f32x4 v = e4[j * kBlock + threadIdx.x];
-#pragma unroll
-                for (int c = 0; c < 4; ++c) p[j][c] = v[c];
-            }
-            valid = 0xffffu;
-        } else {
-            const float *eb = e + r.block0;
-            const uint32_t lo = uint32_t(r.lo - r.block0), hi = uint32_t(r.hi - r.block0);
-#pragma unroll
-            for (int j = 0; j < kVecPerThread; ++j) {
-#pragma unroll
-                for (int c = 0; c < 4; ++c) p[j][c] = 0.0f;
-                if (!slice_meets(j, lo, hi)) continue;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const uint32_t o = tile_off(j, c);
-                    if (o >= lo && o < hi) {
-                        p[j][c] = eb[o];
-                        valid |= 1u << (4 * j + c);
-                    }
-                }
-            }
-        }
+        uint32_t valid;
+        tile_load<false>(nullptr, e, 0.0f, r, p, valid);
         uint32_t emit_mask = 0, cand_mask = 0;
 #pragma unroll
         for (int j = 0; j < kVecPerThread; ++j) {
@@ -1918,7 +1925,6 @@ __device__ void bracket_work(uint2 item, float *__restrict__ e, int32_t *__restr
     }
 }
 
-template <bool kAligned>
 __global__ __launch_bounds__(kBlock) void seg_pass2_kernel(float *__restrict__ e,
                                                            int32_t *__restrict__ idx,
                                                            float *__restrict__ val, int32_t nseg,
@@ -1933,7 +1939,7 @@ __global__ __launch_bounds__(kBlock) void seg_pass2_kernel(float *__restrict__ e
             const uint32_t g1 = min((t1 - 1u) >> ws.sweep_shift, uint32_t(kSweepGroups - 1));
             uint32_t marked = 0u;
             for (uint32_t q = t0 >> ws.sweep_shift; q <= g1; ++q) marked |= ws.sweep[q];
-            if (marked) pass2_tiles<kAligned>(e, idx, val, nseg, ws, t0, t1, hist, sg);
+            if (marked) pass2_tiles(e, idx, val, nseg, ws, t0, t1, hist, sg);
         }
     // work list: workgroup b owns slots b, b + grid, b + 2 grid, ... (a
     // segment's items are consecutive slots, so they spread over workgroups);
@@ -2300,9 +2306,10 @@ hipError_t launch_topk_segmented(const float *g, float *e, int64_t d, float lr, 
     ws.ccap_total = L.ccap_total;
     ws.work_cap = uint32_t(L.work_cap);
     ws.wg_max = nseg > kSegManyMin ? kWgSegMax : kWgSegFew;
-    // every tile index is below ceil(d / kTile) + nseg, so its group is below
-    // kSweepGroups
-    const int64_t max_tiles = (d + kTile - 1) / kTile + nseg;
+    ws.phase = int64_t((reinterpret_cast<uintptr_t>(e) & 127u) / 4u);
+    // every tile index is below ceil((d + phase) / kTile) + nseg, so its group
+    // is below kSweepGroups
+    const int64_t max_tiles = (d + ws.phase + kTile - 1) / kTile + nseg;
     while (((max_tiles - 1) >> ws.sweep_shift) >= kSweepGroups) ++ws.sweep_shift;
 
     // one segment's histograms a workgroup, four workgroups a CU at most
@@ -2325,21 +2332,14 @@ hipError_t launch_topk_segmented(const float *g, float *e, int64_t d, float lr, 
     const int64_t slice_max = nseg > kSearchTwoRounds ? kSliceTilesMaxMany : kSliceTilesMax;
     const int64_t slice = max(int64_t(1), min(slice_max, (max_tiles + wgs - 1) / wgs));
     const uint32_t grid = uint32_t(min(wgs, (max_tiles + slice - 1) / slice));
-    const bool aligned = ((reinterpret_cast<uintptr_t>(g) | reinterpret_cast<uintptr_t>(e)) & 15) == 0;
-    if (aligned)
-        seg_pass1_kernel<true><<<grid, kBlock, 0, stream>>>(g, e, lr, idx, val, nseg, ws, uint32_t(slice));
-    else
-        seg_pass1_kernel<false><<<grid, kBlock, 0, stream>>>(g, e, lr, idx, val, nseg, ws, uint32_t(slice));
+    seg_pass1_kernel<<<grid, kBlock, 0, stream>>>(g, e, lr, idx, val, nseg, ws, uint32_t(slice));
     // one segment a workgroup while that fills the chip at most twice over,
     // then four
     const int32_t nbig = int32_t(min(int64_t(nseg), 4 * cus));
     const int32_t group = nseg <= 8 * cus ? 1 : kWaves;
     seg_select_kernel<<<uint32_t(nbig + (nseg + group - 1) / group), kBlock, 0, stream>>>(
         g, e, lr, idx, val, ws, nseg, nbig, group);
-    if (aligned)
-        seg_pass2_kernel<true><<<grid, kBlock, 0, stream>>>(e, idx, val, nseg, ws, uint32_t(slice));
-    else
-        seg_pass2_kernel<false><<<grid, kBlock, 0, stream>>>(e, idx, val, nseg, ws, uint32_t(slice));
+    seg_pass2_kernel<<<grid, kBlock, 0, stream>>>(e, idx, val, nseg, ws, uint32_t(slice));
     seg_final_kernel<<<uint32_t(min(int64_t(nseg), cus)), kBlock, 0, stream>>>(e, idx, val, ws, nseg);
     return hipGetLastError();
 }

@@ -712,3 +712,45 @@ def test_segmented_single_workgroup_sizes(kind, unaligned):
         assert_bits_equal(gv[o], rv, "t=%d values" % t)
         assert_bits_equal(ge, re, "t=%d e'" % t)
         e = re
+
+
+def _at(a, shift):
+    """A copy of `a` starting `shift` elements into a 256-byte aligned buffer."""
+    buf = torch.empty(a.size + shift, dtype=torch.float32, device=DEV)
+    buf[shift:].copy_(torch.from_numpy(np.ascontiguousarray(a)))
+    return buf[shift:]
+
+
+def _check_steps(gs, off, ks, g_shift=0, e_shift=0, what=""):
+    """Error-feedback calls on one workspace against the oracle."""
+    d, k_total = int(off[-1]), int(np.asarray(ks).sum())
+    off, ks = np.asarray(off, np.int64), np.asarray(ks, np.int64)
+    ws = efs.new_topk_segmented_workspace(ks.size, k_total, DEV)
+    ws.zero_()
+    e = np.zeros(d, np.float32)
+    for t, g in enumerate(gs):
+        gd, ed = _at(g, g_shift), _at(e, e_shift)
+        idx = torch.full((k_total,), -7, dtype=torch.int32, device=DEV)
+        val = torch.full((k_total,), -7.0, dtype=torch.float32, device=DEV)
+        efs.topk_segmented_compress(gd, ed, LR, dev(off), dev(ks), idx, val, ws)
+        assert efs.topk_segmented_status(ws) == 0
+        gi, gv, ge = idx.cpu().numpy(), val.cpu().numpy(), ed.cpu().numpy()
+        ri, rv, re = oracle.topk_segmented(g, e, LR, off, ks)
+        o = np.lexsort((gi, np.repeat(np.arange(ks.size), ks)))
+        np.testing.assert_array_equal(gi[o], ri, "%s t=%d indices" % (what, t))
+        assert_bits_equal(gv[o], rv, "%s t=%d values" % (what, t))
+        assert_bits_equal(ge, re, "%s t=%d e'" % (what, t))
+        e = re
+
+
+@pytest.mark.parametrize("g_shift,e_shift", [(0, 0), (1, 0), (0, 1), (3, 2), (0, 31), (5, 32), (17, 4)])
+def test_segmented_tiles_at_any_alignment(g_shift, e_shift):
+    # segments with tiles whose ends fall on, one before and one after a
+    # block's start as e's line and the segment's offset place it; the first
+    # calls without brackets, the later ones with
+    sizes = [16_385 * 2, 4096 * 5 - 1, 31, 4096 * 6 + 1, 4097, 4096 * 4 + 2, 65_536, 1, 20_000, 4096 - e_shift, 4999]
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    ks = [max(1, s // 500) for s in sizes]
+    say("segmented tiles g_shift=%d e_shift=%d d=%d" % (g_shift, e_shift, off[-1]))
+    _check_steps([synth.small_gradient(6000 + t % 2, int(off[-1])) for t in range(5)], off, ks,
+                 g_shift, e_shift, "tiles")
