@@ -51,7 +51,9 @@
 //            when only some keys equal to T are kept, the lowest indices among
 //            them by a radix select on the index; emits, clears e, and keeps
 //            T as the next hint.  Scan mode does the same over the segment's
-//            elements.  Results never depend on the hint.
+//            elements; a large one is first swept by the whole grid, which
+//            sends the keys above T's 256-key bin and lists those in it.
+//            Results never depend on the hint.
 //
 // Payload: segment s's pairs at [kout[s], kout[s] + min(k[s], size)), kout the
 // exclusive prefix of those counts; order within a segment unspecified.
@@ -136,13 +138,24 @@ static_assert(kFineBins == kDigit2, "the bracket histogram lives in a segment's 
 static_assert(kWidthMax <= 19, "a bracket spans under 2^20 keys, so a bin at most 1024");
 constexpr uint32_t kHintMagic = 0x53454748u;
 
+// Scan-mode segments of more than kScanSharedMin elements are swept by the
+// whole final grid, up to kScanShared of them; one workgroup alone reads such
+// a segment three times, at about 1 us for 2,048 elements.  First call on a
+// workspace, 2.56e7 elements in 161 segments: 729 -> 243 us with the update;
+// 3.3e7 in 297: 1289 -> 268 (574 with the whole grid on one segment after
+// another).  A shorter segment is read by one workgroup, beside the others',
+// in the time of the sweep's round trips.
+constexpr uint32_t kScanShared = 58;
+constexpr int64_t kScanSharedMin = 1 << 16;
+
 struct SegCtl {
     uint32_t status;   // 0: layout accepted; 1: rejected (the call changed nothing)
     uint32_t tiles;    // tiles of all segments
     uint32_t bracket;  // segments that selected from the bracket (a diagnostic)
     uint32_t pass2;    // nonzero when some segment needs pass2's tile sweep
     uint32_t wtotal;   // work-list slots of all segments (bracket path, for pass2)
-    uint32_t pad[59];
+    uint32_t scans;    // large segments in scan mode
+    uint32_t scan[kScanShared];   // the first of them, which the final grid sweeps together
 };
 static_assert(sizeof(SegCtl) == 256, "control block is 256 bytes");
 
@@ -160,11 +173,13 @@ struct SegState {
     uint32_t bracket;  // 1: pass1 collects keys in [lo, hi], emits keys above hi
     uint32_t lo, hi;
     uint32_t shift;    // bracket bin of a key: (key - lo) >> shift, 1024 bins
-    uint32_t da;       // bracket path: the bin holding the k-th key (kNoBin: none needed)
+    uint32_t da;       // bracket path: the bin holding the k-th key (kNoBin: none needed);
+                       // scan mode: 1 when the final grid sweeps the segment together
     uint32_t needa;    // keys of bin da to keep
     uint32_t ca;       // keys in bin da
     uint32_t ecut;     // pairs above the bracket (payload slots 0 .. ecut-1)
-    uint32_t tcur;     // keys of bin da listed by pass2 after the candidates
+    uint32_t tcur;     // keys of bin da listed by pass2 after the candidates; in a
+                       // shared scan, workgroups of the final grid that have finished
     uint32_t miss;     // bracket not used: 1 threshold below it, 2 above it, 3 too many keys in it
 };
 static_assert(sizeof(SegState) == 64, "segment state is 64 bytes");
@@ -739,6 +754,7 @@ __device__ __forceinline__ void reset_publish(const SegWs &ws, const int64_t *of
                         total.w > ws.work_cap;
     ws.ctl->bracket = 0u;
     ws.ctl->pass2 = 0u;
+    ws.ctl->scans = 0u;
     ws.ctl->wtotal = reject ? 0u : total.w;
     ws.ctl->status = reject ? 1u : 0u;
     ws.ctl->tiles = reject ? 0u : total.t;
@@ -1634,6 +1650,13 @@ __device__ void choose_digit1(const SegWs &ws, int32_t s, const SegInfo &inf, Se
         // a flag, stored (an atomic per segment on one word serialises when
         // thousands of segments take this path)
         if (c1 != 0u) ws.ctl->pass2 = 1u;
+        if (int64_t(c1) > inf.ccap && inf.size > kScanSharedMin) {
+            const uint32_t at = atomicAdd(&ws.ctl->scans, 1u);
+            if (at < kScanShared) {
+                ws.ctl->scan[at] = uint32_t(s);
+                st->da = 1u;
+            }
+        }
     }
     const bool sweep = s_out[2] != 0u;
     __syncthreads();  // s_out is reused by the caller
@@ -1977,6 +2000,9 @@ struct FinalShared {
     uint32_t wave[kWaves];
     uint32_t out[3];
     uint32_t cursor;
+    uint32_t fill[2], base[2];  // shared scan: pairs staged for the payload, for the list
+    uint32_t last;
+    uint32_t scan[kScanShared], scan_end[kScanShared];   // shared scans: segments, running step counts
 };
 
 constexpr uint32_t kNone = 0xffffffffu;  // no item (larger than every index)
@@ -2184,7 +2210,7 @@ __device__ __forceinline__ void final_fast_wave(float *__restrict__ e, int32_t *
     if (lane == 0u) *hint = next_hint(oh, T, width);
 }
 
-__device__ void final_segment(float *__restrict__ e, int32_t *__restrict__ idx,
+__device__ __forceinline__ void final_segment(float *__restrict__ e, int32_t *__restrict__ idx,
                               float *__restrict__ val, const SegWs &ws, int32_t s, FinalShared &sh) {
     const SegState st = ws.st[s];
     if (st.mode != kModeCand && st.mode != kModeScan && st.mode != kModeFast) return;
@@ -2227,7 +2253,102 @@ __device__ void final_segment(float *__restrict__ e, int32_t *__restrict__ idx,
     }
 }
 
-// One workgroup per CU at most, looping over the segments b, b + grid, ...
+// Scan-mode segments shared by the grid.  Their elements form one run of steps
+// of 2048, of which every workgroup takes an equal piece (a whole grid for one
+// segment after another would pay each one's round trips in turn).  A
+// workgroup with a piece of segment s finds T's bin of 256 keys from pass2's
+// histogram, sends the keys above the bin (e cleared) and lists those in it in
+// the candidate region.  The last workgroup to finish (no workgroup waits for
+// another) turns the segment into one with listed candidates and returns
+// true: it ranks the list.  When the bin holds more keys than the region (equal
+// keys), the first of them returns true and scans the segment alone.
+constexpr uint32_t kScanStep = uint32_t(kUnroll) * kBlock;
+constexpr uint32_t kScanStage = kCandLds / 2;
+static_assert(kScanStage >= 2 * kScanStep, "a step fits the stage after a check");
+constexpr uint32_t kScanPiece = 4;   // steps a workgroup takes, at least
+static_assert(kScanShared <= uint32_t(kWave), "one lane per shared segment");
+
+__device__ __forceinline__ uint32_t scan_steps(int64_t size) {
+    return uint32_t((size + kScanStep - 1) / kScanStep);
+}
+
+// Steps [from, to) of segment s, one of `sharers` pieces of it.
+__device__ __forceinline__ bool scan_shared(float *e, int32_t *__restrict__ idx,
+                                            float *__restrict__ val, const SegWs &ws, int32_t s,
+                                            uint32_t from, uint32_t to, uint32_t sharers,
+                                            FinalShared &sh) {
+    const uint32_t tid = threadIdx.x;
+    const SegInfo inf = ws.info[s];
+    SegState *st = ws.st + s;
+    const uint32_t d1 = st->d1, need1 = st->need1;
+    for (int b = tid; b < kDigit2; b += kBlock) sh.hist[b] = ws.hist2[int64_t(s) * kDigit2 + b];
+    if (tid < 2) sh.fill[tid] = 0u;
+    __syncthreads();
+    pick_bin<kDigit2, true>(sh.hist, need1, sh.wave, sh.out);
+    const uint32_t bin = (d1 << (kShift1 - kShift2)) | sh.out[0];
+    const uint32_t need = need1 - sh.out[1], count = sh.out[2];
+    __syncthreads();   // sh.out is used again
+    if (int64_t(count) > inf.ccap) return from == 0u;
+    for (uint32_t step = from; step < to; ++step) {
+        const int64_t base = int64_t(step) * kScanStep;
+        uint32_t v[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const int64_t q = base + u * kBlock + tid;
+            v[u] = q < inf.size ? __float_as_uint(e[inf.off + q]) : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const int64_t q = base + u * kBlock + tid;
+            const uint32_t b = (v[u] & 0x7fffffffu) >> kShift2;
+            if (q < inf.size && b >= bin) {
+                const uint32_t part = b > bin ? 0u : 1u;
+                sh.cand[part * kScanStage + atomicAdd(&sh.fill[part], 1u)] =
+                    make_uint2(v[u], uint32_t(inf.off + q));
+            }
+        }
+        __syncthreads();
+        const uint32_t send = sh.fill[0], list = sh.fill[1];
+        __syncthreads();   // read by every thread before it changes
+        if (max(send, list) <= kScanStage - kScanStep && step + 1u < to) continue;
+        if (tid == 0) {
+            sh.base[0] = send != 0u ? atomicAdd(&st->emit, send) : 0u;
+            sh.base[1] = list != 0u ? atomicAdd(&st->ccur, list) : 0u;
+            sh.fill[0] = 0u;
+            sh.fill[1] = 0u;
+        }
+        __syncthreads();
+        for (uint32_t q = tid; q < send; q += kBlock) {
+            const uint2 it = sh.cand[q];
+            const int64_t slot = int64_t(sh.base[0]) + q;
+            if (slot < inf.k) {
+                idx[inf.kout + slot] = int32_t(it.y);
+                val[inf.kout + slot] = __uint_as_float(it.x);
+                e[it.y] = 0.0f;
+            }
+        }
+        for (uint32_t q = tid; q < list; q += kBlock) {
+            const int64_t slot = int64_t(sh.base[1]) + q;
+            if (slot < inf.ccap) ws.cand[inf.coff + slot] = sh.cand[kScanStage + q];
+        }
+        __syncthreads();   // the stage is free
+    }
+    __threadfence();   // this workgroup's part of the list, before its ticket
+    __syncthreads();
+    if (tid == 0) sh.last = atomicAdd(&st->tcur, 1u) == sharers - 1u ? 1u : 0u;
+    __syncthreads();
+    if (sh.last == 0u) return false;
+    __threadfence();
+    if (tid == 0) {
+        st->mode = kModeCand;
+        st->emit = uint32_t(inf.k) - need;
+        st->ccur = count;
+    }
+    __syncthreads();
+    return true;
+}
+
+// One workgroup per CU, looping over the segments b, b + grid, ...
 // (each adds its count to one word at the end, 13 ns apiece: with four a CU a
 // call over 2e4 layers, none of which needs this launch, spent 15 us in it).
 // Most need nothing here (one tile, none,
@@ -2243,10 +2364,35 @@ __global__ __launch_bounds__(kBlock) void seg_final_kernel(float *__restrict__ e
     __shared__ int32_t s_list[kBlock];
     __shared__ uint32_t s_wave[kWaves];
     if (ws.ctl->status != 0u) return;
+    const uint32_t scans = min(ws.ctl->scans, kScanShared);
+    uint64_t mine = 0;  // of them, this workgroup's to finish
+    if (scans != 0u) {
+        if (threadIdx.x < kWave) {
+            const uint32_t seg = threadIdx.x < scans ? ws.ctl->scan[threadIdx.x] : 0u;
+            const uint32_t end =
+                wave_incl_u32(threadIdx.x < scans ? scan_steps(ws.info[seg].size) : 0u);
+            if (threadIdx.x < scans) {
+                sh.scan[threadIdx.x] = seg;
+                sh.scan_end[threadIdx.x] = end;
+            }
+        }
+        __syncthreads();
+        const uint32_t steps = sh.scan_end[scans - 1u];
+        const uint32_t piece = max(kScanPiece, (steps + gridDim.x - 1u) / gridDim.x);
+        const uint32_t p0 = blockIdx.x * piece, p1 = min(steps, p0 + piece);
+        for (uint32_t i = 0; i < scans; ++i) {
+            const uint32_t b0 = i != 0u ? sh.scan_end[i - 1u] : 0u, b1 = sh.scan_end[i];
+            if (p0 >= b1 || p1 <= b0) continue;
+            const uint32_t sharers = (b1 - 1u) / piece - b0 / piece + 1u;
+            if (scan_shared(e, idx, val, ws, int32_t(sh.scan[i]), max(p0, b0) - b0,
+                            min(p1, b1) - b0, sharers, sh))
+                mine |= uint64_t(1) << i;
+        }
+    }
     uint32_t fast = 0;  // segments resolved from the bracket, counted per thread
     const int32_t per = (nseg - int32_t(blockIdx.x) + int32_t(gridDim.x) - 1) / int32_t(gridDim.x);
     const uint32_t wave = threadIdx.x / kWave;
-    for (int32_t g0 = 0; g0 < per; g0 += kBlock) {
+    for (int32_t g0 = 0; g0 < per || mine != 0ull; g0 += kBlock) {
         const int32_t q = g0 + int32_t(threadIdx.x);
         const int32_t s = int32_t(blockIdx.x) + q * int32_t(gridDim.x);
         uint32_t mode = kModeNone, listed = 0u;
@@ -2254,6 +2400,8 @@ __global__ __launch_bounds__(kBlock) void seg_final_kernel(float *__restrict__ e
             const SegState *p = ws.st + s;
             mode = p->mode;
             if (mode == kModeFast) listed = p->needa != 0u ? min(p->ca, p->tcur) : 0u;
+            // taken above (one of them may read as kModeCand by now)
+            if ((mode == kModeScan || mode == kModeCand) && p->da == 1u) mode = kModeNone;
         }
         fast += mode == kModeFast || mode == kModeHit ? 1u : 0u;
         // bracket-path segments with at most kWave keys to rank go to the
@@ -2268,8 +2416,15 @@ __global__ __launch_bounds__(kBlock) void seg_final_kernel(float *__restrict__ e
         __syncthreads();
         for (uint32_t i = wave; i < n_small; i += kWaves)
             final_fast_wave(e, idx, val, ws, s_list[kBlock - 1 - int(i)]);
-        for (uint32_t i = 0; i < n_work; ++i) {
-            final_segment(e, idx, val, ws, s_list[i], sh);
+        for (uint32_t i = 0; i < n_work || mine != 0ull;) {
+            int32_t seg;
+            if (mine != 0ull) {
+                seg = int32_t(sh.scan[__builtin_ctzll(mine)]);
+                mine &= mine - 1ull;
+            } else {
+                seg = s_list[i++];
+            }
+            final_segment(e, idx, val, ws, seg, sh);
             __syncthreads();  // the LDS of this segment is free
         }
     }
@@ -2340,7 +2495,7 @@ hipError_t launch_topk_segmented(const float *g, float *e, int64_t d, float lr, 
     seg_select_kernel<<<uint32_t(nbig + (nseg + group - 1) / group), kBlock, 0, stream>>>(
         g, e, lr, idx, val, ws, nseg, nbig, group);
     seg_pass2_kernel<<<grid, kBlock, 0, stream>>>(e, idx, val, nseg, ws, uint32_t(slice));
-    seg_final_kernel<<<uint32_t(min(int64_t(nseg), cus)), kBlock, 0, stream>>>(e, idx, val, ws, nseg);
+    seg_final_kernel<<<uint32_t(cus), kBlock, 0, stream>>>(e, idx, val, ws, nseg);
     return hipGetLastError();
 }
 

@@ -754,3 +754,27 @@ def test_segmented_tiles_at_any_alignment(g_shift, e_shift):
     say("segmented tiles g_shift=%d e_shift=%d d=%d" % (g_shift, e_shift, off[-1]))
     _check_steps([synth.small_gradient(6000 + t % 2, int(off[-1])) for t in range(5)], off, ks,
                  g_shift, e_shift, "tiles")
+
+
+@pytest.mark.parametrize("kind", ["crowded", "ties", "equal", "many"])
+def test_segmented_large_scan(kind):
+    # more keys under the k-th one's digit than the segment's candidate region
+    # holds, in segments on both sides of the size that the whole grid sweeps
+    # (65,536): distinct keys, keys with ties to split by index, more equal
+    # keys than the region holds, and more such segments than are shared (58)
+    rng = np.random.default_rng(6100)
+    sizes = [65_537 + 977 * i for i in range(62)] + [65_536] * 3 if kind == "many" else [400_003, 65_536, 10, 65_537, 1_300_000]
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    ks = [max(1, s // 4000) for s in sizes]
+    d = int(off[-1])
+
+    def gradient():
+        if kind == "equal":
+            return np.full(d, -2.0, np.float32)
+        g = (1.0 + 0.03 * rng.random(d)).astype(np.float32)
+        if kind == "ties":   # 491 values
+            g = (np.round(g * 16384.0) / 16384.0).astype(np.float32)
+        return np.where(rng.random(d) < 0.5, -g, g).astype(np.float32)
+
+    say("segmented large scan %s d=%d nseg=%d" % (kind, d, len(sizes)))
+    _check_steps([gradient() for _ in range(3)], off, ks, e_shift=1, what="scan " + kind)
