@@ -348,3 +348,33 @@ def test_apply_sgd_one_payload(n):
     assert efs.sparse_status(ws) == efs.SPARSE_BAD_INDEX
     got, _ = run_apply([(one[0][0][:1], one[0][1][:1])], d, efs.APPLY_SGD, x0, ws=ws)
     assert efs.sparse_status(ws) == 0
+
+
+@pytest.mark.parametrize("n,ranges", [(1, 2048), (1, 2049), (3, 682), (3, 1400), (33, 62), (33, 125), (64, 32), (64, 33)])
+def test_apply_packed_scan_tiles(n, ranges):
+    # the packed layout's slots are handed out per 2,048 counters, whole ranges
+    # at a time: counts on either side of one and two such tiles, payloads with
+    # empty ranges, an empty payload among them, and a workspace of unknown
+    # content that is then used again
+    d = 8192 * ranges - 5
+    rng = np.random.default_rng(900 + n + ranges)
+    say("apply packed scan tiles n=%d ranges=%d" % (n, ranges))
+    p_ref = []
+    for w in range(n):
+        k = 0 if w == 1 else min(d, 40_000 // n + 17 * w + 1)
+        i = np.unique(rng.integers(0, d, size=k)).astype(np.int32)
+        i = rng.permutation(np.union1d(i, [d - 1] if w == 0 else []).astype(np.int32))
+        p_ref.append((i, rng.standard_normal(i.size).astype(np.float32)))
+    p_dev = [(dev(i), dev(v)) for i, v in p_ref]
+    x0, m0 = host_state(d, 19)
+    ws = efs.new_apply_workspace(p_dev, d, DEV, layout="packed")
+    ws.copy_(torch.randint(0, 256, ws.shape, dtype=torch.uint8, device=DEV))
+    avg = oracle.accumulate(p_ref, d)
+    want_x, want_m = oracle.update(p_ref, x0, 2, m=m0, beta=BETA, gamma=GAMMA)
+    for rep in range(2):
+        got, _ = run_apply(p_dev, d, efs.APPLY_AVERAGE, x0, ws=ws)
+        assert_bits_equal(got, avg)
+        got_x, got_m = run_apply(p_dev, d, efs.APPLY_MOMENTUM, x0, m0, ws=ws)
+        assert_bits_equal(got_x, want_x)
+        assert_bits_equal(got_m, want_m)
+        assert efs.sparse_status(ws) == 0
