@@ -126,7 +126,10 @@ constexpr int64_t kSmallK = 8;
 // the keys, which takes about 17 barriers and three passes over the registers.
 constexpr int64_t kMaximaK = 48;
 constexpr uint32_t kWgList = 2048;             // elements listed, at most
-constexpr uint32_t kWgRank = 384;              // ... ranked against one another; more by a radix select
+// ... ranked against one another; more by a radix select.  Ranking costs every
+// key a comparison with every other: 2.56e7 elements in 20,000 equal layers,
+// 20 %, 266 us a call so, 533 with a limit of 384.
+constexpr uint32_t kWgRank = kBlock / 2;
 // Flags of groups of consecutive tiles (2^sweep_shift tiles a group, at most
 // kSweepGroups groups): select1 marks the groups of the segments that need
 // pass2's tile sweep, and pass2 skips every slice whose groups are unmarked.
@@ -1121,8 +1124,8 @@ __device__ __forceinline__ void list_mine(WgShared &sh, uint32_t mine, uint32_t 
 
 // Of the n listed elements (k <= n <= kWgList; larger key first, then lower
 // index) the first k go to the payload, e cleared at them (their p was written
-// before the caller's last barrier), and sh.T gets the k-th key.  A few are
-// ranked against one another, more by a radix select on the key (bits 30..20,
+// before the caller's last barrier), and sh.T gets the k-th key.  Up to kWgRank
+// are ranked against one another, more by a radix select on the key (bits 30..20,
 // 19..10, 9..0) and, when only some of the keys equal to the threshold are
 // kept, on the offset (bits 13..3, 2..0).  `hist` as for select_in_wg.
 __device__ __forceinline__ void rank_listed(WgShared &sh, uint32_t n, uint32_t k,
@@ -1135,16 +1138,32 @@ __device__ __forceinline__ void rank_listed(WgShared &sh, uint32_t n, uint32_t k
         es[it.y] = 0.0f;
     };
     if (n <= kWgRank) {
-        for (uint32_t i = tid; i < n; i += kBlock) {
-            const uint2 it = sh.item[i];
-            const uint32_t key = it.x & 0x7fffffffu;
-            uint32_t r = 0u;
-#pragma unroll 8
-            for (uint32_t q = 0; q < n; ++q) {
-                const uint2 v = sh.item[q];
-                const uint32_t vk = v.x & 0x7fffffffu;
-                r += (vk > key || (vk == key && v.y < it.y)) ? 1u : 0u;
+        // 2^part_log threads an element, each against its share of the others,
+        // kReads of them read at once (those past n are in the array and count
+        // for nothing).  No `&&` or `||`: as branches each key waits for its own
+        // two reads, 300 cycles a key (500 layers of 4,000 elements, 5 %: the
+        // launch 77 us, 20 without a hint, 12 so).
+        const uint32_t part_log = n <= uint32_t(kBlock) / 4u ? 2u : 1u;
+        const uint32_t parts = 1u << part_log, i = tid >> part_log;
+        const uint2 it = sh.item[i];
+        const uint32_t key = it.x & 0x7fffffffu;
+        uint32_t r = 0u;
+        constexpr uint32_t kReads = 8;
+        static_assert(kWgRank + 4u * kReads <= kWgList, "reads past the list stay in the array");
+#pragma unroll 1
+        for (uint32_t q0 = (tid & (parts - 1u)) * kReads; q0 < n; q0 += kReads * parts) {
+            uint2 v[kReads];
+#pragma unroll
+            for (uint32_t u = 0; u < kReads; ++u) v[u] = sh.item[q0 + u];
+#pragma unroll
+            for (uint32_t u = 0; u < kReads; ++u) {
+                const uint32_t vk = v[u].x & 0x7fffffffu;
+                r += (uint32_t(vk > key) | (uint32_t(vk == key) & uint32_t(v[u].y < it.y))) &
+                     uint32_t(q0 + u < n);
             }
+        }
+        for (uint32_t x = parts >> 1; x != 0u; x >>= 1) r += __shfl_xor(r, int(x));
+        if (i < n && (tid & (parts - 1u)) == 0u) {
             if (r < k) send(r, it);
             if (r == k - 1u) sh.T = key;
         }

@@ -714,6 +714,44 @@ def test_segmented_single_workgroup_sizes(kind, unaligned):
         e = re
 
 
+@pytest.mark.parametrize("nseg,size,rho", [(500, 4000, 0.05), (4000, 1000, 0.2)])
+def test_segmented_hints_do_not_slow_a_call(nseg, size, rho):
+    # a call with hints lists and ranks a little more than k elements a layer,
+    # one without selects among all of them: the first must not be the slower
+    # one (ranking that took its reads one by one made it 3 times slower).  The
+    # least of several times, with a margin for the box
+    d = nseg * size
+    off = dev(np.arange(nseg + 1, dtype=np.int64) * size)
+    ks = dev(np.full(nseg, int(size * rho), np.int64))
+    k_total = nseg * int(size * rho)
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    gs = [torch.randn(d, generator=gen, device=DEV) for _ in range(2)]
+    # a settled residual: uniform below the threshold, along the mean gradient
+    e0 = torch.rand(d, generator=gen, device=DEV).mul_(0.1 * 0.56 / rho).copysign_(gs[0] + gs[1])
+    idx = torch.empty(k_total, dtype=torch.int32, device=DEV)
+    val = torch.empty(k_total, dtype=torch.float32, device=DEV)
+    ws = efs.new_topk_segmented_workspace(nseg, k_total, DEV)
+
+    def times(keep_hints, n=12):
+        e, out = e0.clone(), []
+        ws.zero_()
+        for t in range(n):
+            if not keep_hints:
+                ws.zero_()
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            efs.topk_segmented_compress(gs[t % 2], e, LR, off, ks, idx, val, ws)
+            b.record()
+            torch.cuda.synchronize()
+            out.append(a.elapsed_time(b) * 1e3)
+        return min(out[2:])
+    times(True, 3)
+    hinted, fresh = times(True), times(False)
+    say("segmented %d layers of %d: %.1f us with hints, %.1f without" % (nseg, size, hinted, fresh))
+    assert efs.topk_segmented_status(ws) == 0
+    assert hinted <= 1.4 * fresh + 5.0
+
+
 def _at(a, shift):
     """A copy of `a` starting `shift` elements into a 256-byte aligned buffer."""
     buf = torch.empty(a.size + shift, dtype=torch.float32, device=DEV)
