@@ -26,16 +26,17 @@
 //            smoothly; the bracket reaches 2^wl keys below the prediction and
 //            2^wh above, each 2^12..2^19, adapted per segment), keys above hi
 //            go straight to the payload, keys inside it to the candidates and
-//            to a 1024-bin histogram of the bracket.
-//   select   the segments without tiles, step and selection in one read of g
-//            and e; those a workgroup selects list the keys not below their
-//            bracket's lower end while they are formed.  And, one workgroup
-//            per segment with tiles: when pass1 had a bracket and its counts
-//            prove the k-th key inside it, the bracket bin da holding it, and
-//            pass2's work items for the segment.  Otherwise the digit D1
-//            holding the k-th key and the mode: none (k = 0), all (k = size),
-//            candidates (the keys in D1 fit the segment's candidate region) or
-//            scan (they do not: a large set of equal or nearly equal
+//            to a 1024-bin histogram of the bracket.  Beside the sweep, by
+//            workgroups of their own, the segments without tiles (in the next
+//            launch when there are very many): step and selection in one read
+//            of g and e; those a workgroup selects list the keys not below
+//            their bracket's lower end while they are formed.
+//   select   one workgroup per segment with tiles: when pass1 had a bracket and
+//            its counts prove the k-th key inside it, the bracket bin da
+//            holding it, and pass2's work items for the segment.  Otherwise the
+//            digit D1 holding the k-th key and the mode: none (k = 0), all
+//            (k = size), candidates (the keys in D1 fit the segment's candidate
+//            region) or scan (they do not: a large set of equal or nearly equal
 //            magnitudes).
 //   pass2    radix path, a read of p (4 B/element): keys above D1 go to the
 //            payload and their e to +0 (mode all: every key); keys in D1 are
@@ -87,11 +88,23 @@ enum : uint32_t {
 // tiles, wherever it starts: when only the segments inside one 4096-element
 // block were selected so, a fifth of 2e4 layers, cut in two by a block
 // boundary, took the path of the large ones (2.56e7 elements: 276 us a step,
-// 125 so).  Up to kSegManyMin segments, which leave most of the chip idle,
-// the limit is one 4096-element read: a longer segment's reads in turn would
-// hold up the launch (161 layers over 2.56e7 elements: 19 us, 9 so).
+// 125 so).  Up to kSegFew segments the limit is one 4096-element read: with
+// little else to do, the launch would wait for the longer segments' reads in
+// turn (1e6 elements in 30 segments: 35 us a call, 39 with the longer limit; the
+// first call on a workspace over 4.1e6 in 300: 76 and 98; over 4.1e6 in 700, 1 %,
+// 85 and 75).
 constexpr int64_t kWgSegMax = 16384, kWgSegFew = 4096;
-constexpr int32_t kSegManyMin = 1024;
+constexpr int32_t kSegFew = 512;
+
+// Up to kBesideMax segments the whole segments are selected in pass 1's launch,
+// their workgroups first: their chains of round trips pass while the others
+// sweep.  In a launch of their own after it they were the larger part of a call
+// with few or mid-size layers (us a call, after / beside: 1e5 elements in 100
+// layers 36 / 31, 4.1e6 in 1,500 76 / 67, 1.65e7 in 2,500 130 / 99, 6e7 in 5,000
+// 266 / 231).  Far more segments fill the chip several times over by themselves,
+// and there five workgroups a CU (27 KB of LDS) beat pass 1's four: 2.56e7 in
+// 20,000 110 / 119, 1.65e7 in 12,000 91 / 96, in 7,000 122 / 115.
+constexpr int32_t kBesideMax = 8192;
 
 // log2 of how far the bracket reaches below and above the predicted
 // threshold, each adapted per segment between these (2^19 keys are 3-6 % of
@@ -1547,9 +1560,71 @@ __device__ __forceinline__ void select_in_wave(const float *__restrict__ g, floa
     }
 }
 
+// The segments without tiles among the `group` (at most kWaves) consecutive ones
+// from s0 on, step and selection: a wave each where a wave can, the rest by the
+// workgroup one after another.  `hist` is 2048 words of LDS.  Called by every
+// thread of the workgroup.
+__device__ __forceinline__ void whole_group(const float *__restrict__ g, float *e, float lr,
+                                            int32_t *__restrict__ idx, float *__restrict__ val,
+                                            const SegWs &ws, int32_t nseg, int32_t s0,
+                                            int32_t group, uint32_t *hist, WgShared &wsh) {
+    const int32_t wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave);
+    // the group's tables and hints, a dword a lane (one round trip): lanes
+    // 16 i .. 16 i + 15 hold segment s0 + i's SegInfo, 8 i .. 8 i + 7 its hint
+    constexpr int kInfoWords = sizeof(SegInfo) / 4, kHintWords = sizeof(SegHint) / 4;
+    static_assert(kWaves * kInfoWords == kWave, "one wave holds a group's tables");
+    const int lane = threadIdx.x & (kWave - 1);
+    const int32_t have = min(group, nseg - s0);
+    uint32_t tab = 0u, hints = 0u;
+    if (lane / kInfoWords < have)
+        tab = reinterpret_cast<const uint32_t *>(ws.info + s0 + lane / kInfoWords)[lane % kInfoWords];
+    if (lane / kHintWords < have)
+        hints = reinterpret_cast<const uint32_t *>(ws.hint + s0 + lane / kHintWords)[lane % kHintWords];
+    if (wave < have) {
+        const SegInfo inf = tab_info(tab, kInfoWords * wave);
+        if (inf.size > 0 && wave_layer(inf.size, inf.k)) select_in_wave(g, e, lr, idx, val, inf);
+    }
+    for (int b = threadIdx.x; b < 2048; b += kBlock) hist[b] = 0u;
+#pragma unroll 1
+    for (int32_t i = 0; i < have; ++i) {
+        const int32_t s = s0 + i;
+        const SegInfo inf = tab_info(tab, kInfoWords * i);
+        if (inf.size > ws.wg_max || wave_layer(inf.size, inf.k)) continue;
+        SegHint oh = {};
+        oh.key = tab_word(hints, kHintWords * i);
+        oh.prev = tab_word(hints, kHintWords * i + 1);
+        oh.prev2 = tab_word(hints, kHintWords * i + 2);
+        oh.magic = tab_word(hints, kHintWords * i + 3);
+        oh.width = tab_word(hints, kHintWords * i + 4);
+        const bool hinted = hint_usable(oh);
+        Bracket br = {0u, 0u};
+        if (hinted) br = bracket_of(oh);
+        __syncthreads();   // wsh and hist are free
+        uint32_t listed;
+        bool inside;
+        const uint32_t T = select_in_wg(g, e, lr, idx, val, inf, hinted, br, listed, inside, hist,
+                                        wsh);
+        if (threadIdx.x == 0 && T != kNoThreshold) {
+            // both sides wider after the threshold fell outside the bracket,
+            // the lower one narrower after a list well over k
+            const uint32_t w0 = hinted ? oh.width : make_widths(kWidthStart, kWidthStart);
+            uint32_t wl = width_lo(w0), wh = width_hi(w0);
+            if (hinted && !inside) {
+                wl = min(wl + 1u, kWidthMax);
+                wh = min(wh + 1u, kWidthMax);
+            } else if (hinted && int64_t(listed) > 2 * inf.k + 24 && wl > kWidthMin) {
+                --wl;
+            }
+            ws.hint[s] = next_hint(oh, T, make_widths(wl, wh));
+            if (inside && listed <= kWgList) ws.st[s].mode = kModeHit;
+        }
+    }
+}
+
 // Tiles [t0, t1) of pass1; every selection, count and histogram is flushed
-// before it returns (the LDS histogram is left zero).
-__device__ void pass1_slice(const float *__restrict__ g, float *__restrict__ e, float lr,
+// before it returns (the LDS histogram is left zero).  Inlined: a call costs
+// 152 bytes of scratch a lane and 10 us a sweep over 1.65e7 elements.
+__device__ __forceinline__ void pass1_slice(const float *__restrict__ g, float *__restrict__ e, float lr,
                             int32_t *__restrict__ idx, float *__restrict__ val, int32_t nseg,
                             const SegWs &ws, uint32_t t0, uint32_t t1, uint32_t *hist, Stage &sg) {
     int32_t s = segment_of_tile(ws.tile_prefix, nseg, t0);
@@ -1623,17 +1698,26 @@ __device__ void pass1_slice(const float *__restrict__ g, float *__restrict__ e, 
     __syncthreads();  // the next slice starts with another segment's state
 }
 
-__global__ __launch_bounds__(kBlock, 4) void seg_pass1_kernel(const float *__restrict__ g,
-                                                           float *__restrict__ e, float lr,
-                                                           int32_t *__restrict__ idx,
-                                                           float *__restrict__ val, int32_t nseg,
-                                                           SegWs ws, uint32_t slice) {
-    __shared__ uint32_t hist[kDigit1];
+// kBeside: the first `whole` workgroups select the segments without tiles
+// (`group` each), the others sweep.
+template <bool kBeside>
+__global__ __launch_bounds__(kBlock, 4) void seg_pass1_kernel(
+    const float *__restrict__ g, float *__restrict__ e, float lr, int32_t *__restrict__ idx,
+    float *__restrict__ val, int32_t nseg, SegWs ws, uint32_t slice, uint32_t whole,
+    int32_t group) {
+    __shared__ __align__(16) uint32_t hist[kDigit1];
     __shared__ Stage sg;
     if (ws.ctl->status != 0u) return;
+    if (kBeside && blockIdx.x < whole) {
+        static_assert(2048 * 4 + sizeof(WgShared) <= sizeof(hist), "the whole segments' LDS");
+        whole_group(g, e, lr, idx, val, ws, nseg, int32_t(blockIdx.x) * group, group, hist,
+                    *reinterpret_cast<WgShared *>(hist + 2048));
+        return;
+    }
     const uint32_t T = ws.ctl->tiles;
+    const uint32_t step = (gridDim.x - whole) * slice;
     for (int b = threadIdx.x; b < kDigit1; b += kBlock) hist[b] = 0u;
-    for (uint32_t t0 = blockIdx.x * slice; t0 < T; t0 += gridDim.x * slice)
+    for (uint32_t t0 = (blockIdx.x - whole) * slice; t0 < T; t0 += step)
         pass1_slice(g, e, lr, idx, val, nseg, ws, t0, min(T, t0 + slice), hist, sg);
 }
 
@@ -1755,10 +1839,9 @@ __device__ void select1_segment(const SegWs &ws, int32_t s, uint32_t *s_wave, ui
 
 // The first `nbig` workgroups take the segments with tiles: each reads the
 // tile counts of up to kBlock of its segments b, b + nbig, ... at once and
-// works through those that have any.  The others take `group` consecutive
-// segments each and select those without tiles, which pass1 left alone: a
-// wave each where a wave can, the rest by the workgroup one after another.
-// Both kinds in one launch: the first keep few CUs busy for a few round trips.
+// works through those that have any.  The others, if any, take `group`
+// consecutive segments each and select those without tiles, which pass1 left
+// alone.
 __global__ __launch_bounds__(kBlock, 5) void seg_select_kernel(const float *__restrict__ g, float *e,
                                                             float lr, int32_t *__restrict__ idx,
                                                             float *__restrict__ val, SegWs ws,
@@ -1785,58 +1868,7 @@ __global__ __launch_bounds__(kBlock, 5) void seg_select_kernel(const float *__re
         }
         return;
     }
-    const int32_t s0 = (int32_t(blockIdx.x) - nbig) * group;
-    const int32_t wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave);
-    // the group's tables and hints, a dword a lane (one round trip): lanes
-    // 16 i .. 16 i + 15 hold segment s0 + i's SegInfo, 8 i .. 8 i + 7 its hint
-    constexpr int kInfoWords = sizeof(SegInfo) / 4, kHintWords = sizeof(SegHint) / 4;
-    static_assert(kWaves * kInfoWords == kWave, "one wave holds a group's tables");
-    const int lane = threadIdx.x & (kWave - 1);
-    const int32_t have = min(group, nseg - s0);
-    uint32_t tab = 0u, hints = 0u;
-    if (lane / kInfoWords < have)
-        tab = reinterpret_cast<const uint32_t *>(ws.info + s0 + lane / kInfoWords)[lane % kInfoWords];
-    if (lane / kHintWords < have)
-        hints = reinterpret_cast<const uint32_t *>(ws.hint + s0 + lane / kHintWords)[lane % kHintWords];
-    if (wave < have) {
-        const SegInfo inf = tab_info(tab, kInfoWords * wave);
-        if (inf.size > 0 && wave_layer(inf.size, inf.k)) select_in_wave(g, e, lr, idx, val, inf);
-    }
-    for (int b = threadIdx.x; b < 2048; b += kBlock) hist[b] = 0u;
-#pragma unroll 1
-    for (int32_t i = 0; i < have; ++i) {
-        const int32_t s = s0 + i;
-        const SegInfo inf = tab_info(tab, kInfoWords * i);
-        if (inf.size > ws.wg_max || wave_layer(inf.size, inf.k)) continue;
-        SegHint oh = {};
-        oh.key = tab_word(hints, kHintWords * i);
-        oh.prev = tab_word(hints, kHintWords * i + 1);
-        oh.prev2 = tab_word(hints, kHintWords * i + 2);
-        oh.magic = tab_word(hints, kHintWords * i + 3);
-        oh.width = tab_word(hints, kHintWords * i + 4);
-        const bool hinted = hint_usable(oh);
-        Bracket br = {0u, 0u};
-        if (hinted) br = bracket_of(oh);
-        __syncthreads();   // wsh and hist are free
-        uint32_t listed;
-        bool inside;
-        const uint32_t T = select_in_wg(g, e, lr, idx, val, inf, hinted, br, listed, inside, hist,
-                                        wsh);
-        if (threadIdx.x == 0 && T != kNoThreshold) {
-            // both sides wider after the threshold fell outside the bracket,
-            // the lower one narrower after a list well over k
-            const uint32_t w0 = hinted ? oh.width : make_widths(kWidthStart, kWidthStart);
-            uint32_t wl = width_lo(w0), wh = width_hi(w0);
-            if (hinted && !inside) {
-                wl = min(wl + 1u, kWidthMax);
-                wh = min(wh + 1u, kWidthMax);
-            } else if (hinted && int64_t(listed) > 2 * inf.k + 24 && wl > kWidthMin) {
-                --wl;
-            }
-            ws.hint[s] = next_hint(oh, T, make_widths(wl, wh));
-            if (inside && listed <= kWgList) ws.st[s].mode = kModeHit;
-        }
-    }
+    whole_group(g, e, lr, idx, val, ws, nseg, (int32_t(blockIdx.x) - nbig) * group, group, hist, wsh);
 }
 
 // ---------------------------------------------------------------------------
@@ -2479,7 +2511,7 @@ hipError_t launch_topk_segmented(const float *g, float *e, int64_t d, float lr, 
     ws.sweep = reinterpret_cast<uint32_t *>(base + L.sweep);
     ws.ccap_total = L.ccap_total;
     ws.work_cap = uint32_t(L.work_cap);
-    ws.wg_max = nseg > kSegManyMin ? kWgSegMax : kWgSegFew;
+    ws.wg_max = nseg > kSegFew ? kWgSegMax : kWgSegFew;
     ws.phase = int64_t((reinterpret_cast<uintptr_t>(e) & 127u) / 4u);
     // every tile index is below ceil((d + phase) / kTile) + nseg, so its group
     // is below kSweepGroups
@@ -2506,12 +2538,19 @@ hipError_t launch_topk_segmented(const float *g, float *e, int64_t d, float lr, 
     const int64_t slice_max = nseg > kSearchTwoRounds ? kSliceTilesMaxMany : kSliceTilesMax;
     const int64_t slice = max(int64_t(1), min(slice_max, (max_tiles + wgs - 1) / wgs));
     const uint32_t grid = uint32_t(min(wgs, (max_tiles + slice - 1) / slice));
-    seg_pass1_kernel<<<grid, kBlock, 0, stream>>>(g, e, lr, idx, val, nseg, ws, uint32_t(slice));
-    // one segment a workgroup while that fills the chip at most twice over,
-    // then four
+    // whole segments: one a workgroup while that fills the chip at most twice
+    // over, then four
     const int32_t nbig = int32_t(min(int64_t(nseg), 4 * cus));
     const int32_t group = nseg <= 8 * cus ? 1 : kWaves;
-    seg_select_kernel<<<uint32_t(nbig + (nseg + group - 1) / group), kBlock, 0, stream>>>(
+    const uint32_t groups = uint32_t((nseg + group - 1) / group);
+    const bool beside = nseg <= kBesideMax;
+    if (beside)
+        seg_pass1_kernel<true><<<groups + grid, kBlock, 0, stream>>>(g, e, lr, idx, val, nseg, ws,
+                                                                     uint32_t(slice), groups, group);
+    else
+        seg_pass1_kernel<false><<<grid, kBlock, 0, stream>>>(g, e, lr, idx, val, nseg, ws,
+                                                             uint32_t(slice), 0u, group);
+    seg_select_kernel<<<uint32_t(nbig) + (beside ? 0u : groups), kBlock, 0, stream>>>(
         g, e, lr, idx, val, ws, nseg, nbig, group);
     seg_pass2_kernel<<<grid, kBlock, 0, stream>>>(e, idx, val, nseg, ws, uint32_t(slice));
     seg_final_kernel<<<uint32_t(cus), kBlock, 0, stream>>>(e, idx, val, ws, nseg);

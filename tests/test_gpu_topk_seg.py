@@ -673,30 +673,46 @@ def test_segmented_randomised_ef_loops(seed):
     say("  bracket segments per step: %s" % hits)
 
 
+def _tiles(ws):
+    """Tiles of the last call's segments (the word after the status)."""
+    off = int(efs.load_library().topk_segmented_status_offset()) + 4
+    return int(ws[off:off + 4].cpu().numpy().view("<u4")[0])
+
+
 @pytest.mark.parametrize("kind", ["gauss", "ties", "equal"])
 @pytest.mark.parametrize("unaligned", [False, True])
-def test_segmented_single_workgroup_sizes(kind, unaligned):
+@pytest.mark.parametrize("nseg", [127, 512, 513, 8192, 8193])
+def test_segmented_single_workgroup_sizes(kind, unaligned, nseg):
     # sizes and budgets at the edges of the ways a segment is selected whole:
     # by a wave (1,024 elements, k = 8), from the threads' maxima (k = 48), by
-    # a radix select, from its hint's list (up to 384 and 2,048 elements), in
-    # one to four 4096-element pieces, and the first size that has tiles
-    # (16,385).  Four calls carry the error, so the later ones have hints; with
-    # ties (grid, lr = 1) equal keys are split by index
+    # a radix select, from its hint's list (up to 128 and 2,048 elements), in
+    # one to four 4096-element pieces, and the first size that has tiles: 4,097
+    # up to 512 segments, 16,385 above (tiny ones make up the number), beside the
+    # sweep up to 8,192 segments and after it above.  Four calls carry the error,
+    # so the later ones have hints; with ties (grid, lr = 1) equal keys are
+    # split by index, across the pieces too
     rng = np.random.default_rng(5100)
     sizes, ks = [], []
     for size in (1, 3, 255, 1023, 1024, 1025, 4095, 4096, 4097, 8193, 12_288, 16_383, 16_384, 16_385):
-        for k in (1, 8, 9, 48, 49, 300, 385, 2048, 2049, size - 1, size):
+        for k in (1, 8, 9, 48, 49, 64, 65, 128, 129, 300, 2048, 2049, size - 1, size):
             if 0 < k <= size:
                 sizes.append(size)
                 ks.append(k)
-    order = rng.permutation(len(sizes))
-    sizes, ks = np.array(sizes, np.int64)[order], np.array(ks, np.int64)[order]
+    order = rng.permutation(len(sizes))[:nseg]
+    order = np.concatenate([order, np.full(nseg - order.size, -1)])
+    order = order[rng.permutation(nseg)]
+    sizes = np.where(order < 0, rng.integers(1, 5, nseg), np.array(sizes, np.int64)[order])
+    ks = np.where(order < 0, 1, np.array(ks, np.int64)[order])
     off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
     d, k_total = int(off[-1]), int(ks.sum())
+    limit, phase = (4096 if nseg <= 512 else 16_384), (1 if unaligned else 0)
+    blocks = (off[1:] + phase - 1) // 4096 - (off[:-1] + phase) // 4096 + 1
+    want_tiles = int(blocks[sizes > limit].sum())
+    assert want_tiles > 0 and (sizes == limit).any()
     ws = efs.new_topk_segmented_workspace(ks.size, k_total, DEV)
     ws.zero_()
     e = np.zeros(d, np.float32)
-    say("segmented single-workgroup sizes %s unaligned=%s d=%d nseg=%d" % (kind, unaligned, d, ks.size))
+    say("segmented single-workgroup sizes %s unaligned=%s d=%d nseg=%d" % (kind, unaligned, d, nseg))
     for t in range(4):
         if kind == "gauss":
             g = synth.small_gradient(5200 + t, d)
@@ -705,7 +721,7 @@ def test_segmented_single_workgroup_sizes(kind, unaligned):
         else:
             g = np.full(d, -2.0, np.float32)
         gi, gv, ge, _ = run_gpu(g, e, off, ks, k_total=k_total, ws=ws, unaligned=unaligned)
-        assert efs.topk_segmented_status(ws) == 0
+        assert efs.topk_segmented_status(ws) == 0 and _tiles(ws) == want_tiles
         ri, rv, re = oracle.topk_segmented(g, e, LR, off, ks)
         o = np.lexsort((gi, np.repeat(np.arange(ks.size), ks)))
         np.testing.assert_array_equal(gi[o], ri, "t=%d indices" % t)
