@@ -1084,12 +1084,14 @@ __device__ __forceinline__ void stage_tile(Stage &sg, uint32_t &efill, uint32_t 
 // LDS of a workgroup selecting a segment in registers (beside 2048 words of
 // zeroed histogram, left zero).
 struct WgShared {
-    uint32_t best[kBlock];      // a thread's largest key + 1 (0: it has no element)
+    alignas(16) uint32_t best[kBlock];   // a thread's largest key + 1 (0: it has no element)
     uint2 item[kWgList];        // (bits of p, offset in the segment)
     uint32_t wave[kWaves];
     uint32_t out[3];
     uint32_t count, above, cut, T;
 };
+static_assert(alignof(WgShared) >= 16 && offsetof(WgShared, best) % 16 == 0,
+              "maxima_cut reads best 16 bytes at a time");
 
 // The k-th largest of the threads' `best` (0 for a thread without elements),
 // as a key: at least k elements are not below it.  0 when fewer than k
