@@ -247,11 +247,10 @@ __global__ __launch_bounds__(kBlock) void apply_group_kernel(Payloads p, int32_t
     // the last call on this workspace left every counter tagged for this
     // epoch with count 0: plain atomic adds suffice
     const bool clean = ctl->clean == clean_key(epoch, entries);
-    if (threadIdx.x == 0) s_flags = 0u;
-    __syncthreads();
     bool truncated;
     const int64_t c = payload_len(p, w, truncated);
-    if (truncated && blockIdx.x == 0 && threadIdx.x == 0) s_flags |= kSparseTruncated;
+    if (threadIdx.x == 0) s_flags = truncated && blockIdx.x == 0 ? kSparseTruncated : 0u;
+    __syncthreads();
     const int32_t *__restrict__ idx = p.idx[w];
     const float *__restrict__ val = p.val[w];
     const int lane = threadIdx.x & (kWave - 1);
@@ -306,7 +305,7 @@ static_assert(kMaxApplyWorkers <= kScanTile, "a range's counters fit a tile");
 __global__ __launch_bounds__(kBlock) void apply_scan_kernel(
     const unsigned long long *__restrict__ cnt, uint32_t *__restrict__ start, int64_t entries,
     int64_t tile, ApplyCtl *__restrict__ ctl) {
-    __shared__ __align__(16) uint32_t s_v[kScanTile];
+    __shared__ uint32_t s_v[kScanTile];
     __shared__ uint32_t s_wave[kWaves];
     __shared__ uint32_t s_base;
     const int tid = threadIdx.x;

@@ -378,3 +378,32 @@ def test_apply_packed_scan_tiles(n, ranges):
         assert_bits_equal(got_x, want_x)
         assert_bits_equal(got_m, want_m)
         assert efs.sparse_status(ws) == 0
+
+
+@pytest.mark.parametrize("layout", ["bucketed", "packed"])
+@pytest.mark.parametrize("n", [1, 2])
+def test_apply_reports_truncation_and_bad_index_together(n, layout):
+    # both faults in one payload, the bad index in each wave of the first
+    # workgroup in turn: each is noted by its own threads, neither may lose
+    # the other's bit
+    d, cap = 50_000, 300
+    rng = np.random.default_rng(91)
+    good = rng.permutation(d)[:cap].astype(np.int32)
+    val = rng.standard_normal(cap).astype(np.float32)
+    ctr = efs.new_counter(DEV)
+    ctr[0] = cap + 1
+    clean = (dev(good), dev(val))
+    x0, _ = host_state(d, 92)
+    for at in (0, 63, 64, 200, cap - 1):
+        bad = good.copy()
+        bad[at] = d
+        p_dev = [(dev(bad), dev(val), ctr)] + [clean] * (n - 1)
+        keep = np.arange(cap) != at
+        ref = [(good[keep], val[keep])] + [(good, val)] * (n - 1)
+        ws = efs.new_apply_workspace(p_dev, d, DEV, layout=layout)
+        for mode, want in ((efs.APPLY_AVERAGE, oracle.accumulate(ref, d)),
+                           (efs.APPLY_SGD, oracle.update(ref, x0, 1)[0])):
+            for rep in range(4):
+                got, _ = run_apply(p_dev, d, mode, x0, ws=ws)
+                assert efs.sparse_status(ws) == efs.SPARSE_TRUNCATED | efs.SPARSE_BAD_INDEX
+                assert_bits_equal(got, want)
