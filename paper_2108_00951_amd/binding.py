@@ -313,6 +313,11 @@ def _payload_arrays(payloads: Sequence[Tuple]):
     return idx_arr, val_arr, cnt_arr, caps
 
 
+def _held(payloads: Sequence[Tuple]):
+    """The payloads' tensors, whatever the caller does with its own lists."""
+    return tuple(tuple(p) for p in payloads)
+
+
 def sparse_accumulate(payloads: Sequence[Tuple], d: int, out, workspace, stream=None) -> None:
     """Average of n payloads into out; see sparse_accumulate in include/efsparse.h.
 
@@ -386,7 +391,7 @@ def prepare_sparse_apply(payloads: Sequence[Tuple], d: int, mode: int, x, worksp
 
     def call():
         _check(lib, fn(*args))
-    call.tensors = (tuple(payloads), x, m, workspace)   # alive as long as the pointers in args
+    call.tensors = (_held(payloads), x, m, workspace)   # alive as long as the pointers in args
     return call
 
 
@@ -413,7 +418,7 @@ def prepare_sparse_accumulate(payloads: Sequence[Tuple], d: int, out, workspace,
 
     def call():
         _check(lib, fn(*args))
-    call.tensors = (tuple(payloads), out, workspace)   # alive as long as the pointers in args
+    call.tensors = (_held(payloads), out, workspace)   # alive as long as the pointers in args
     return call
 
 

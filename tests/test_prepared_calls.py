@@ -1,6 +1,6 @@
 """A prepared call keeps the tensors whose pointers it holds alive: a program
-may drop its own references (a workspace passed as a temporary, say) and go
-on calling.  Runs on the CPU with a stand-in for the library."""
+may drop its own references (a workspace passed as a temporary, a list of
+payloads that it fills anew) and go on calling.  Runs on the CPU with a stand-in for the library."""
 import gc
 import weakref
 
@@ -20,8 +20,9 @@ class _Library:
     sparse_accumulate = sparse_apply
 
 
+@pytest.mark.parametrize("as_list", [False, True])
 @pytest.mark.parametrize("kind", ["accumulate", "sgd", "momentum"])
-def test_prepared_call_keeps_its_tensors(kind, monkeypatch):
+def test_prepared_call_keeps_its_tensors(kind, as_list, monkeypatch):
     monkeypatch.setattr(efs, "load_library", lambda *a: _Library)
     monkeypatch.setattr(efs, "_require", lambda *a: torch)
     monkeypatch.setattr(efs, "_stream_handle", lambda s: 0)
@@ -32,14 +33,18 @@ def test_prepared_call_keeps_its_tensors(kind, monkeypatch):
     if kind == "momentum":
         tensors["m"] = torch.zeros(d)
     t = tensors
-    payloads = [(t["idx"], t["val"], t["counter"])]
+    payload = (t["idx"], t["val"], t["counter"])
+    payloads = [list(payload) if as_list else payload]
     if kind == "accumulate":
         call = efs.prepare_sparse_accumulate(payloads, d, t["x"], t["ws"])
     else:
         mode = efs.APPLY_SGD if kind == "sgd" else efs.APPLY_MOMENTUM
         call = efs.prepare_sparse_apply(payloads, d, mode, t["x"], t["ws"], m=t.get("m"))
     alive = [weakref.ref(v) for v in tensors.values()]
-    del tensors, t, payloads
+    if as_list:   # the caller's own list, put to another use
+        payloads[0].clear()
+        payloads.clear()
+    del tensors, t, payload, payloads
     gc.collect()
     call()
     assert all(r() is not None for r in alive)
