@@ -780,14 +780,16 @@ def test_topk_views_at_any_alignment(d, shift_g, shift_e):
     assert bool((buf[:shift_e] == 7.0).all()) and bool((buf[shift_e + d:] == 7.0).all())
 
 
-@pytest.mark.parametrize("ties", [100, 128, 129, 512, 513, 2048, 2049, 16_384, 16_385, 60_000])
+@pytest.mark.parametrize("ties", [100, 119, 120, 512, 513, 2039, 2040, 16_375, 16_376, 60_000])
 @pytest.mark.parametrize("at_zero", [False, True])
 def test_topk_threshold_bin_sizes(ties, at_zero):
-    # `ties` coordinates share the threshold's key and half of them are kept:
-    # each way the threshold's bin is ranked (in registers, by histogram, by
-    # index select, by the ordered sweep), on the radix path and from the
-    # bracket, with larger keys before and behind them and, in the bin itself,
-    # a few keys just above the tied one
+    # `ties` coordinates share the threshold's key and half of them are kept,
+    # with larger keys before and behind them and, in the threshold's bin
+    # itself, nine keys just above the tied one.  The bin's total is on both
+    # sides of each way it is ranked: all keys against one another (128), keys
+    # in registers (2,048), a list (16,384 at this d), the ordered sweep; 512
+    # ties are ranked against one another, more by an index select.  First on
+    # the radix path, then from the bracket
     d = 150_001
     rng = np.random.default_rng(ties)
     base = np.float32(0.0 if at_zero else 1.0)
@@ -804,6 +806,7 @@ def test_topk_threshold_bin_sizes(ties, at_zero):
         g[at[ties + 1009:]] = -3.0   # every other coordinate is sent
     k = int((np.abs(g) > base).sum()) + ties // 2
     st = TopkState(d, k)
+    st.ws.zero_()   # no thresholds of an earlier test in it
     zero = np.zeros(d, np.float32)
     want = None
     for t in range(3):
@@ -813,6 +816,10 @@ def test_topk_threshold_bin_sizes(ties, at_zero):
         want = (ri, rv, re)
         assert_payload_equal(st.idx[:k].cpu().numpy(), st.val[:k].cpu().numpy(), ri, rv, "call %d" % t)
         assert_bits_equal(st.e.cpu().numpy(), re, "call %d" % t)
+        # without a list the sweep reads e again, where a bin of zero would
+        # show the coordinates already cleared: the radix path
+        bracket = t > 0 and not (at_zero and ties + near.size > 16_384)
+        assert efs.topk_took_bracket_path(st.ws) == bracket, "call %d" % t
 
 
 @pytest.mark.parametrize("shift_g,shift_e", [(0, 0), (1, 1), (0, 3), (2, 0), (31, 31)])

@@ -673,9 +673,10 @@ def test_segmented_randomised_ef_loops(seed):
     say("  bracket segments per step: %s" % hits)
 
 
-def _tiles(ws):
-    """Tiles of the last call's segments (the word after the status)."""
-    off = int(efs.load_library().topk_segmented_status_offset()) + 4
+def _ctl_word(ws, i):
+    """Word i of the control block after a call: 0 status, 1 tiles of all
+    segments, 5 large segments in scan mode."""
+    off = int(efs.load_library().topk_segmented_status_offset()) + 4 * i
     return int(ws[off:off + 4].cpu().numpy().view("<u4")[0])
 
 
@@ -721,7 +722,7 @@ def test_segmented_single_workgroup_sizes(kind, unaligned, nseg):
         else:
             g = np.full(d, -2.0, np.float32)
         gi, gv, ge, _ = run_gpu(g, e, off, ks, k_total=k_total, ws=ws, unaligned=unaligned)
-        assert efs.topk_segmented_status(ws) == 0 and _tiles(ws) == want_tiles
+        assert efs.topk_segmented_status(ws) == 0 and _ctl_word(ws, 1) == want_tiles
         ri, rv, re = oracle.topk_segmented(g, e, LR, off, ks)
         o = np.lexsort((gi, np.repeat(np.arange(ks.size), ks)))
         np.testing.assert_array_equal(gi[o], ri, "t=%d indices" % t)
@@ -776,18 +777,20 @@ def _at(a, shift):
 
 
 def _check_steps(gs, off, ks, g_shift=0, e_shift=0, what=""):
-    """Error-feedback calls on one workspace against the oracle."""
+    """Error-feedback calls on one workspace against the oracle; returns each
+    call's number of large segments in scan mode."""
     d, k_total = int(off[-1]), int(np.asarray(ks).sum())
     off, ks = np.asarray(off, np.int64), np.asarray(ks, np.int64)
     ws = efs.new_topk_segmented_workspace(ks.size, k_total, DEV)
     ws.zero_()
-    e = np.zeros(d, np.float32)
+    e, scans = np.zeros(d, np.float32), []
     for t, g in enumerate(gs):
         gd, ed = _at(g, g_shift), _at(e, e_shift)
         idx = torch.full((k_total,), -7, dtype=torch.int32, device=DEV)
         val = torch.full((k_total,), -7.0, dtype=torch.float32, device=DEV)
         efs.topk_segmented_compress(gd, ed, LR, dev(off), dev(ks), idx, val, ws)
         assert efs.topk_segmented_status(ws) == 0
+        scans.append(_ctl_word(ws, 5))
         gi, gv, ge = idx.cpu().numpy(), val.cpu().numpy(), ed.cpu().numpy()
         ri, rv, re = oracle.topk_segmented(g, e, LR, off, ks)
         o = np.lexsort((gi, np.repeat(np.arange(ks.size), ks)))
@@ -795,6 +798,7 @@ def _check_steps(gs, off, ks, g_shift=0, e_shift=0, what=""):
         assert_bits_equal(gv[o], rv, "%s t=%d values" % (what, t))
         assert_bits_equal(ge, re, "%s t=%d e'" % (what, t))
         e = re
+    return scans
 
 
 @pytest.mark.parametrize("g_shift,e_shift", [(0, 0), (1, 0), (0, 1), (3, 2), (0, 31), (5, 32), (17, 4)])
@@ -831,4 +835,7 @@ def test_segmented_large_scan(kind):
         return np.where(rng.random(d) < 0.5, -g, g).astype(np.float32)
 
     say("segmented large scan %s d=%d nseg=%d" % (kind, d, len(sizes)))
-    _check_steps([gradient() for _ in range(3)], off, ks, e_shift=1, what="scan " + kind)
+    scans = _check_steps([gradient() for _ in range(3)], off, ks, e_shift=1, what="scan " + kind)
+    say("  large segments in scan mode: %s" % scans)
+    # no bracket in the first call: each segment above 65,536
+    assert scans[0] == sum(s > 65_536 for s in sizes) == (62 if kind == "many" else 3)
