@@ -822,6 +822,30 @@ def test_topk_threshold_bin_sizes(ties, at_zero):
         assert efs.topk_took_bracket_path(st.ws) == bracket, "call %d" % t
 
 
+@pytest.mark.parametrize("kept", [2047, 2048, 2049, 5000, 8192])
+@pytest.mark.parametrize("equal", [False, True])
+def test_topk_dense_spans(kept, equal):
+    # the radix path's sweeps where 8192-element spans hold `kept` kept keys:
+    # below, at and above what a workgroup stages (2,048), all of them; more
+    # equal keys than the list holds (16,384) are sent by the ordered sweep
+    d = 8192 * 5 + 77
+    rng = np.random.default_rng(kept)
+    g = (rng.random(d) * 0.5).astype(np.float32)
+    for lo in (0, 8192, 3 * 8192):
+        at = lo + rng.permutation(8192)[:kept]
+        g[at] = np.float32(2.0) if equal else (2.0 + rng.random(kept)).astype(np.float32)
+    k = 3 * kept - (1 if equal else 0)   # equal keys: not all of them
+    st = TopkState(d, k)
+    for t in range(2):
+        st.ws.zero_()   # the radix path
+        st.e.zero_()
+        efs.topk_compress(to_dev(g), st.e, 1.0, k, st.idx, st.val, st.ws)
+        ri, rv, re = oracle.topk(g, np.zeros(d, np.float32), np.float32(1.0), k)
+        assert not efs.topk_took_bracket_path(st.ws)
+        assert_payload_equal(st.idx.cpu().numpy(), st.val.cpu().numpy(), ri, rv, "call %d" % t)
+        assert_bits_equal(st.e.cpu().numpy(), re, "call %d" % t)
+
+
 @pytest.mark.parametrize("shift_g,shift_e", [(0, 0), (1, 1), (0, 3), (2, 0), (31, 31)])
 @pytest.mark.parametrize("d", [1, 33, 4096, 4127, 8192, 1_000_003])
 def test_ht_views_at_any_alignment(d, shift_g, shift_e):
