@@ -73,12 +73,6 @@ uint32_t balanced_grid(int64_t work_tiles, int workgroups_per_cu) {
     return uint32_t((work_tiles + per_wg - 1) / per_wg);
 }
 
-uint32_t persistent_grid(int64_t work_tiles) {
-    const int64_t cap = int64_t(device_cu_count()) * 8;
-    if (work_tiles < 1) work_tiles = 1;
-    return uint32_t(work_tiles < cap ? work_tiles : cap);
-}
-
 }  // namespace efs
 
 extern "C" {

@@ -129,7 +129,7 @@ struct Layout {
 
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// ctl | cnt[entries] | (packed: start[entries + 1]) | pair slots
+// ctl | cnt[entries] | (packed: start[entries]) | pair slots
 Layout make_layout(int32_t n, int64_t d, int64_t total_cap, bool bucketed) {
     Layout L;
     const int64_t range = int64_t(1) << (bucketed ? kBucketRangeLog : kPackedRangeLog);
@@ -141,7 +141,7 @@ Layout make_layout(int32_t n, int64_t d, int64_t total_cap, bool bucketed) {
         L.pair_off = L.start_off;
         L.pair_slots = L.entries * range;
     } else {
-        L.pair_off = L.start_off + round_up(size_t(L.entries + 1) * 4, 256);
+        L.pair_off = L.start_off + round_up(size_t(L.entries) * 4, 256);
         L.pair_slots = total_cap;
     }
     L.bytes = L.pair_off + size_t(L.pair_slots) * 8;

@@ -17,13 +17,9 @@ constexpr int kWaves = kBlock / kWave;
 constexpr int kVecPerThread = 4;         // float4 per thread per tile
 constexpr int kTile = kBlock * kVecPerThread * 4;   // 4096 elements per tile
 
-// Resident workgroups per compute unit assumed by the grid sizing
-// (balanced_grid): the hard-threshold pass (two 4-wave workgroups per CU
-// measured fastest), kernels staging pairs in LDS (up to 33 KiB each), and
-// histogram / scan passes.
+// Resident workgroups per compute unit of the hard-threshold pass, for its grid
+// (balanced_grid): two 4-wave workgroups measured fastest.
 constexpr int kHtWorkgroupsPerCU = 2;
-constexpr int kStageWorkgroupsPerCU = 4;
-constexpr int kScanWorkgroupsPerCU = 8;
 
 // The tiles a workgroup of a persistent grid takes: first, first + stride,
 // ... below end.  Plain: tile b, b + G, b + 2G, ... (the resident workgroups
@@ -178,12 +174,6 @@ struct PairStageN {
 };
 using PairStage = PairStageN<kTile>;
 
-// Flushes the `fill` staged pairs to payload slots reserved by one atomic on
-// `word`.  With `last` the workgroup also takes its ticket; the workgroup
-// holding the final ticket (all others have added their pairs by then)
-// publishes the total to *count when count is non-null, and returns `word`
-// to zero for the next call.  Slots at or past `cap` are not written.
-// Called by every thread of the workgroup; contains barriers.
 // Error-feedback telemetry accumulated across calls (layout of the C ABI's
 // telemetry object): the total error sum_t ||e_{t+1}||^2 as kTelemetryParts
 // partial sums (workgroup b adds into part b mod kTelemetryParts: one binary64
@@ -200,6 +190,12 @@ struct Telemetry {
 };
 static_assert(sizeof(Telemetry) == 288, "telemetry object layout");
 
+// Flushes the `fill` staged pairs to payload slots reserved by one atomic on
+// `word`.  With `last` the workgroup also takes its ticket; the workgroup
+// holding the final ticket (all others have added their pairs by then)
+// publishes the total to *count when count is non-null, and returns `word`
+// to zero for the next call.  Slots at or past `cap` are not written.
+// Called by every thread of the workgroup; contains barriers.
 template <int N>
 __device__ __forceinline__ void stage_flush(PairStageN<N> &st, uint32_t fill, bool last,
                                             unsigned long long *word, uint32_t *count,
@@ -231,57 +227,6 @@ __device__ __forceinline__ void stage_flush(PairStageN<N> &st, uint32_t fill, bo
         }
     }
     __syncthreads();
-}
-
-// Appends the elements of one tile selected by `mask` (bit 4*j + c for
-// element (j, c) of this thread; index tile0 + (j*kBlock + tid)*4 + c, value
-// v[j][c]) to the stage, flushing first when they might not fit.  A tile
-// with more selected elements than the stage holds is written straight to
-// the payload behind its own atomic.  `fill` is identical in all threads.
-// Called by every thread of the workgroup; contains barriers.
-template <int N>
-__device__ __forceinline__ void stage_mask(PairStageN<N> &st, uint32_t &fill, uint32_t mask,
-                                           const float (&v)[kVecPerThread][4], int64_t tile0,
-                                           unsigned long long *word, uint64_t cap,
-                                           int32_t *__restrict__ idx, float *__restrict__ val) {
-    uint32_t total;
-    const uint32_t pos = block_prefix_small(__popc(mask), st.wave, total);
-    if (total == 0) return;
-    const bool direct = total > uint32_t(N);
-    if (direct || fill + total > uint32_t(N)) {
-        stage_flush(st, fill, false, word, nullptr, cap, idx, val);
-        fill = 0;
-    }
-    uint64_t o = fill + pos;
-    if (direct) {
-        // stage_flush ended with a barrier, so st.base is free to reuse
-        if (threadIdx.x == 0) st.base = atomicAdd(word, (unsigned long long)total) & kCountMask;
-        __syncthreads();
-        o += st.base;
-    }
-#pragma unroll
-    for (int j = 0; j < kVecPerThread; ++j) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            if ((mask >> (4 * j + c)) & 1u) {
-                const int32_t i = int32_t(tile0 + int64_t(j * kBlock + int(threadIdx.x)) * 4 + c);
-                if (direct) {
-                    if (o < cap) {
-                        idx[o] = i;
-                        val[o] = v[j][c];
-                    }
-                } else {
-                    st.idx[o] = i;
-                    st.val[o] = v[j][c];
-                }
-                ++o;
-            }
-        }
-    }
-    if (direct)
-        __syncthreads();  // st.base is read above before any later flush rewrites it
-    else
-        fill += total;
 }
 
 }  // namespace efs

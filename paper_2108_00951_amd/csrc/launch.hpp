@@ -51,10 +51,6 @@ hipError_t launch_copy(const float *src, float *dst, int64_t n, bool per_tile, h
 hipError_t launch_stream_probe(const float *x, float *y, int64_t n, int mode, bool per_tile,
                                hipStream_t stream);
 
-// Workgroups for a grid-stride pass over `work_tiles` tiles: enough to fill
-// every compute unit several times over, never more than there is work.
-uint32_t persistent_grid(int64_t work_tiles);
-
 // Compute units of the current device (queried once per device).
 int device_cu_count();
 
