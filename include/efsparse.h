@@ -209,14 +209,17 @@ efs_status topk_segmented_compress(const float *g, float *e, int64_t d, float lr
  *                bytes: the control block, an 8-byte counter and a 4-byte
  *                segment start per (range, worker), and 8 bytes per payload
  *                slot for the pairs grouped by range.  Four launches.
- *              Both give the same bits.  Contents need no initialisation:
- *              each counter carries the 40-bit epoch of the call that wrote
- *              it (the control block's epoch, advanced by every call), so a
- *              counter of an earlier call reads as zero, as does arbitrary
- *              content except when its epoch bits equal the current epoch
- *              (probability 2^-40 per counter for random bytes).  Calls on
- *              one workspace must be ordered (one stream, or synchronised
- *              streams); concurrent calls on one workspace race.
+ *              Both give the same bits.  (sparse_apply's EFS_APPLY_SGD with
+ *              one payload uses neither: one launch, and words of the control
+ *              block with an epoch of their own.)  Contents need no
+ *              initialisation: each counter carries the 40-bit epoch of the
+ *              call that wrote it (the control block's epoch, advanced by
+ *              every call that uses the counters), so a counter of an earlier
+ *              call reads as zero, as does arbitrary content except when its
+ *              epoch bits equal the current epoch (probability 2^-40 per
+ *              counter for random bytes).  Calls on one workspace must be
+ *              ordered (one stream, or synchronised streams); concurrent
+ *              calls on one workspace race.
  * Payload entries with an index outside [0, d) are skipped and reported in
  * the status word (EFS_SPARSE_BAD_INDEX).  The status word is the uint32 at
  * sparse_status_offset() in the workspace: the EFS_SPARSE_* bits of the last

@@ -289,8 +289,8 @@ __global__ __launch_bounds__(kBlock) void apply_group_kernel(Payloads p, int32_t
     }
 }
 
-// Packed layout: start[e] = the first slot of segment e.  A workgroup takes the
-// counters of `per` consecutive ranges (at most kScanTile), scans them in LDS
+// Packed layout: start[e] = the first slot of segment e.  A workgroup takes
+// `tile` counters, those of whole ranges (at most kScanTile), scans them in LDS
 // and reserves their slots with one atomic, so that a range's segments lie
 // side by side, worker after worker; in which order the workgroups' pieces
 // follow one another matters to nobody (a range's first slot is its first
@@ -628,7 +628,11 @@ __global__ __launch_bounds__(kBlock) void apply_range_kernel(RangeArgs a) {
 // write each.  Against the place and range launches: 1.5e6 pairs over 1.5e9
 // coordinates 526 -> 92 us, 1.1e6 over 1.1e8 133 -> 58, 25,557 over 25.6e6
 // 14.6 -> 5.9, 50 over 5,000 6.0 -> 2.2 (the range launch visits every range
-// of d, here only the payload is read).
+// of d, here only the payload is read).  The line is drawn at no density or
+// order: against those launches at 0.03 to 100 % of 1e6, 2.56e7 and 1.1e8
+// coordinates, pairs in a compressing pass's order or shuffled, x in the caches or
+// out of them, 0.02 to 0.94 of their time, and once 1.01 (1.1e8 coordinates,
+// 3 %, pass order, cold: 132 us).
 // The last workgroup to finish publishes the status word.  One word of
 // tickets would serialise the grid's atomics at 13 ns each, so they go to
 // kDirectTickets words first and the last of each takes one of the final word.

@@ -8,7 +8,7 @@
 // little from one iteration to the next.  Five launches, always all enqueued
 // (work a call does not need returns at once):
 //
-//   reset  zero the control block and histograms (90 KB); form the key
+//   reset  zero the control block and histograms (114,688 bytes); form the key
 //          bracket [lo, hi] around the threshold predicted from the previous
 //          calls on this workspace, as wide as their predictions were off
 //          (kHalfMin .. kHalfMax keys either side).
@@ -333,7 +333,7 @@ struct Pass1Shared {
 // Appends this tile's `total` selected elements (bits of `mask`, this
 // thread's from `pos` on) to a stage, flushing first when they might not fit;
 // a tile with more than the stage holds is written straight out behind its
-// own atomic.  As stage_mask, after the prefix sums.
+// own atomic.  Called by every thread of the workgroup; contains barriers.
 template <int N>
 __device__ __forceinline__ void stage_append(PairStageN<N> &st, uint32_t &fill, uint32_t mask,
                                              uint32_t pos, uint32_t total,

@@ -136,7 +136,8 @@ constexpr int64_t kSmallK = 8;
 // One workgroup selects a segment with k at most kMaximaK among the elements
 // not below the k-th largest of its threads' maxima (at least k of them, and
 // hardly more), ranked against one another; a larger k by a radix select on
-// the keys, which takes about 17 barriers and three passes over the registers.
+// the keys, which takes about 17 barriers and reads the segment's e back four
+// times.
 constexpr int64_t kMaximaK = 48;
 constexpr uint32_t kWgList = 2048;             // elements listed, at most
 // ... ranked against one another; more by a radix select.  Ranking costs every
@@ -234,9 +235,8 @@ __device__ __forceinline__ SegHint next_hint(const SegHint &old, uint32_t T, uin
     return h;
 }
 
-// The reset forms a bracket for a segment from its hint when the segment
-// spans several tiles, keeps some but not all of its elements, and the
-// hint is well formed.
+// The reset forms a bracket for a segment from its hint when the segment has
+// tiles, keeps some but not all of its elements, and the hint is well formed.
 __device__ __forceinline__ bool hint_usable(const SegHint &h) {
     return h.magic == kHintMagic && h.key <= 0x7fffffffu && h.prev <= 0x7fffffffu &&
            h.prev2 <= 0x7fffffffu && widths_ok(h.width);
@@ -727,9 +727,9 @@ __device__ __forceinline__ Sums reset_chunk(const SegWs &ws, const SegIn &in, in
     return tot;
 }
 
-// Zeroes the sweep flags and the histograms of the layers of several tiles (a
-// one-tile layer is selected inside pass1), workgroup w of nw.  An invalid
-// layout is rejected, so what is zeroed for it does not matter.
+// Zeroes the sweep flags and the histograms of the layers with tiles, workgroup
+// w of nw.  An invalid layout is rejected, so what is zeroed for it does not
+// matter.
 __device__ __forceinline__ void reset_zero(const SegWs &ws, const int64_t *off, int32_t nseg,
                                            int32_t w, int32_t nw) {
     const f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -1081,8 +1081,8 @@ __device__ __forceinline__ void stage_tile(Stage &sg, uint32_t &efill, uint32_t 
     __syncthreads();
 }
 
-// LDS of a workgroup selecting a segment in registers (beside 2048 words of
-// zeroed histogram, left zero).
+// LDS of a workgroup selecting a segment whole (beside 2048 words of zeroed
+// histogram, left zero).
 struct WgShared {
     alignas(16) uint32_t best[kBlock];   // a thread's largest key + 1 (0: it has no element)
     uint2 item[kWgList];        // (bits of p, offset in the segment)
@@ -1491,9 +1491,9 @@ __device__ __forceinline__ bool wave_layer(int64_t size, int64_t k) {
 }
 
 // One wave: the error-feedback step and the selection of segment `inf`
-// (one tile, 1 <= size <= kWaveLayerMax): element q * 64 + lane of the
+// (without tiles, 1 <= size <= kWaveLayerMax): element q * 64 + lane of the
 // segment in slot q of the lane, k rounds of a wave-wide maximum of (key,
-// lower index first) as in select_in_tile, the kept pairs written to the
+// lower index first), the kept pairs written to the
 // segment's payload region in index order, e' = p elsewhere and +0 at them.
 __device__ __forceinline__ void select_in_wave(const float *__restrict__ g, float *__restrict__ e,
                                                float lr, int32_t *__restrict__ idx,
@@ -2404,8 +2404,8 @@ __device__ __forceinline__ bool scan_shared(float *e, int32_t *__restrict__ idx,
 // One workgroup per CU, looping over the segments b, b + grid, ...
 // (each adds its count to one word at the end, 13 ns apiece: with four a CU a
 // call over 2e4 layers, none of which needs this launch, spent 15 us in it).
-// Most need nothing here (one tile, none,
-// all), so the workgroup first reads the modes of up to kBlock of its
+// Most need nothing here (selected
+// whole, none, all), so the workgroup first reads the modes of up to kBlock of its
 // segments at once and then runs only those with something to rank (one
 // dependent read per segment in turn was the larger cost with thousands of
 // segments).
