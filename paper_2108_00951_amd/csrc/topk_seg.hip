@@ -96,15 +96,21 @@ enum : uint32_t {
 constexpr int64_t kWgSegMax = 16384, kWgSegFew = 4096;
 constexpr int32_t kSegFew = 512;
 
-// Up to kBesideMax segments the whole segments are selected in pass 1's launch,
-// their workgroups first: their chains of round trips pass while the others
-// sweep.  In a launch of their own after it they were the larger part of a call
-// with few or mid-size layers (us a call, after / beside: 1e5 elements in 100
-// layers 36 / 31, 4.1e6 in 1,500 76 / 67, 1.65e7 in 2,500 130 / 99, 6e7 in 5,000
-// 266 / 231).  Far more segments fill the chip several times over by themselves,
-// and there five workgroups a CU (27 KB of LDS) beat pass 1's four: 2.56e7 in
-// 20,000 110 / 119, 1.65e7 in 12,000 91 / 96, in 7,000 122 / 115.
-constexpr int32_t kBesideMax = 8192;
+// Where the whole segments are selected.  In pass 1's launch, their workgroups
+// first, their chains of round trips pass while the others sweep; in a launch of
+// their own after it they were the larger part of a call with few or mid-size
+// layers (us a call, after / beside: 1e5 elements in 100 layers 36 / 31, 4.1e6 in
+// 1,500 76 / 64, 1.65e7 in 2,500 130 / 99, 6e7 in 5,000 266 / 231).  But there five
+// workgroups a CU (27 KB of LDS) run, beside pass 1's only four, and that decides
+// once they fill the chip several times over: 2.56e7 in 20,000 layers 110 / 119,
+// 1.65e7 in 12,000 91 / 96, in 7,000 122 / 115.  So: beside up to kBesideMax
+// segments, after it above.  With more than kBesideFew of more than kBesideMean
+// elements on average both launches have the workgroups and the device decides:
+// with tiles for less than an eighth of the elements there is no sweep to hide
+// behind (5,000 equal layers over 6e7: 148 / 158, the first call 195 / 229).
+// Shorter ones fill the chip less and gain beside (1e6 in 2,500: 41 / 39).
+constexpr int32_t kBesideFew = 2048, kBesideMax = 8192;
+constexpr int64_t kBesideMean = 2048;
 
 // log2 of how far the bracket reaches below and above the predicted
 // threshold, each adapted per segment between these (2^19 keys are 3-6 % of
@@ -282,8 +288,15 @@ struct SegWs {
     uint32_t work_cap;
     uint32_t sweep_shift;   // tile t is in group t >> sweep_shift
     int64_t wg_max;         // longest segment without tiles
+    uint32_t own_below;     // whole segments take a launch of their own below so many tiles
     int64_t phase;          // elements of e's first 128-byte line before e
 };
+
+// The control block's status and tile count, in one read.
+__device__ __forceinline__ uint2 ctl_words(const SegWs &ws) {
+    static_assert(offsetof(SegCtl, status) == 0 && offsetof(SegCtl, tiles) == 4, "two words");
+    return *reinterpret_cast<const uint2 *>(ws.ctl);
+}
 
 struct SegLayout {
     size_t info, tile_prefix, st, hint, hist1, hist2, cand, work, chunks, sweep, bytes;
@@ -1709,14 +1722,16 @@ __global__ __launch_bounds__(kBlock, 4) void seg_pass1_kernel(
     int32_t group) {
     __shared__ __align__(16) uint32_t hist[kDigit1];
     __shared__ Stage sg;
-    if (ws.ctl->status != 0u) return;
+    const uint2 ctl = ctl_words(ws);
+    if (ctl.x != 0u) return;
+    const uint32_t T = ctl.y;
     if (kBeside && blockIdx.x < whole) {
+        if (T < ws.own_below) return;   // the next launch takes them
         static_assert(2048 * 4 + sizeof(WgShared) <= sizeof(hist), "the whole segments' LDS");
         whole_group(g, e, lr, idx, val, ws, nseg, int32_t(blockIdx.x) * group, group, hist,
                     *reinterpret_cast<WgShared *>(hist + 2048));
         return;
     }
-    const uint32_t T = ws.ctl->tiles;
     const uint32_t step = (gridDim.x - whole) * slice;
     for (int b = threadIdx.x; b < kDigit1; b += kBlock) hist[b] = 0u;
     for (uint32_t t0 = (blockIdx.x - whole) * slice; t0 < T; t0 += step)
@@ -1842,8 +1857,7 @@ __device__ void select1_segment(const SegWs &ws, int32_t s, uint32_t *s_wave, ui
 // The first `nbig` workgroups take the segments with tiles: each reads the
 // tile counts of up to kBlock of its segments b, b + nbig, ... at once and
 // works through those that have any.  The others, if any, take `group`
-// consecutive segments each and select those without tiles, which pass1 left
-// alone.
+// consecutive segments each and select those without tiles, unless pass1 did.
 __global__ __launch_bounds__(kBlock, 5) void seg_select_kernel(const float *__restrict__ g, float *e,
                                                             float lr, int32_t *__restrict__ idx,
                                                             float *__restrict__ val, SegWs ws,
@@ -1852,7 +1866,8 @@ __global__ __launch_bounds__(kBlock, 5) void seg_select_kernel(const float *__re
     __shared__ uint32_t hist[2048];
     __shared__ WgShared wsh;
     __shared__ int32_t s_list[kBlock];
-    if (ws.ctl->status != 0u) return;
+    const uint2 ctl = ctl_words(ws);
+    if (ctl.x != 0u) return;
     if (int32_t(blockIdx.x) < nbig) {
         const int32_t per = (nseg - int32_t(blockIdx.x) + nbig - 1) / nbig;
         for (int32_t g0 = 0; g0 < per; g0 += kBlock) {
@@ -1870,6 +1885,7 @@ __global__ __launch_bounds__(kBlock, 5) void seg_select_kernel(const float *__re
         }
         return;
     }
+    if (ctl.y >= ws.own_below) return;   // pass1 took them
     whole_group(g, e, lr, idx, val, ws, nseg, (int32_t(blockIdx.x) - nbig) * group, group, hist, wsh);
 }
 
@@ -2546,13 +2562,15 @@ hipError_t launch_topk_segmented(const float *g, float *e, int64_t d, float lr, 
     const int32_t group = nseg <= 8 * cus ? 1 : kWaves;
     const uint32_t groups = uint32_t((nseg + group - 1) / group);
     const bool beside = nseg <= kBesideMax;
+    const bool own = !beside || (nseg > kBesideFew && d > kBesideMean * nseg);
+    ws.own_below = !beside ? UINT32_MAX : own ? uint32_t(d / kTile / 8) : 0u;
     if (beside)
         seg_pass1_kernel<true><<<groups + grid, kBlock, 0, stream>>>(g, e, lr, idx, val, nseg, ws,
                                                                      uint32_t(slice), groups, group);
     else
         seg_pass1_kernel<false><<<grid, kBlock, 0, stream>>>(g, e, lr, idx, val, nseg, ws,
                                                              uint32_t(slice), 0u, group);
-    seg_select_kernel<<<uint32_t(nbig) + (beside ? 0u : groups), kBlock, 0, stream>>>(
+    seg_select_kernel<<<uint32_t(nbig) + (own ? groups : 0u), kBlock, 0, stream>>>(
         g, e, lr, idx, val, ws, nseg, nbig, group);
     seg_pass2_kernel<<<grid, kBlock, 0, stream>>>(e, idx, val, nseg, ws, uint32_t(slice));
     seg_final_kernel<<<uint32_t(cus), kBlock, 0, stream>>>(e, idx, val, ws, nseg);

@@ -769,6 +769,23 @@ def test_segmented_hints_do_not_slow_a_call(nseg, size, rho):
     assert hinted <= 1.4 * fresh + 5.0
 
 
+@pytest.mark.parametrize("large", [0, 1, 40])
+def test_segmented_whole_layers_beside_or_after(large):
+    # 2,100 layers of more than 2,048 elements on average: with (almost) no
+    # layer that has tiles the whole ones are selected in a launch of their own,
+    # with enough of them beside the sweep; three calls, the later ones with
+    # hints and brackets
+    rng = np.random.default_rng(7100 + large)
+    sizes = rng.integers(1900, 2500, size=2100)
+    sizes[rng.choice(2100, large, replace=False)] = rng.integers(16_385, 60_000, size=large)
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    d = int(off[-1])
+    assert d > 2048 * sizes.size
+    ks = np.where(rng.random(2100) < 0.1, 0, np.maximum(1, sizes // rng.integers(20, 900, size=2100)))
+    say("segmented beside or after large=%d d=%d" % (large, d))
+    _check_steps([synth.small_gradient(7200 + t % 2, d) for t in range(3)], off, ks, what="large %d" % large)
+
+
 def _at(a, shift):
     """A copy of `a` starting `shift` elements into a 256-byte aligned buffer."""
     buf = torch.empty(a.size + shift, dtype=torch.float32, device=DEV)
