@@ -725,8 +725,8 @@ def bench_radix(efs, torch, synth, cur, wl, dev, calls=4):
     """Top-k from a fresh workspace (no threshold recorded, so the radix path)
     with e = 0 on the workload's first gradient: as drawn, and rounded to
     multiples of 2^-16 and 2^-10, which put ties at the threshold that must
-    be split by index (a few hundred, listed; tens of thousands, counted per
-    tile).  Each call timed alone with events on the stream it runs on."""
+    be split by index (a few hundred, and tens of thousands; both fit the list
+    that one workgroup ranks).  Each call timed alone with events on the stream it runs on."""
     import numpy as np
     d, k = wl.d, wl.topk_k[0]
     host = synth.Stream(wl.ident).gradient(0, threads=min(16, os.cpu_count() or 1))
